@@ -688,7 +688,7 @@ int step_tail(const Fwd& f, const dard_params* params, int b, int B, const void*
 
     const int max_rows = hidden ? b * B : rows;
     int32_t plan[4];
-    gemm_plan(dt, max_rows, V, D, false, frag, plan, true);
+    gemm_plan(dt, max_rows, V, D, false, frag, plan);
     if (!hidden && plan[0] == DARD_GEMM_STREAM) {
         EpiArgs e{};
         e.kind = EPI_STORE_F32; e.y = logits; e.ldy = V;

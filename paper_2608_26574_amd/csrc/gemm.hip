@@ -25,7 +25,7 @@
 //   gemm_pipe: 64 < M < 256 with fragment-major X, 128 x 128 tiles through a
 //     register ring and an LDS double buffer.
 //   gemm_big: M >= 256 with fragment-major X (prefill, large batches), tiles of
-//     up to 256 x 128 / 128 x 256 fed by global_load_lds slice stages.
+//     128 x 192 and others, X through LDS, the weights straight to registers.
 //   gemm_tiled: row-major X (dard_linear), 128 x 128 tiles through LDS.
 #include "common.h"
 #include "launch.h"
@@ -456,83 +456,101 @@ __global__ __launch_bounds__(256, WN <= 4 ? 2 : 1) void gemm_pipe_bf16(const bf1
 }
 
 // ---------------------------------------------------------------- large tiles
-// M >= 256 (prefill of long prefixes, large batches) with fragment-major X.
-// A workgroup of 4 waves (2 x 2) owns a (32 TI)-token x (32 TJ)-column output
-// tile; wave (wm, wn) computes 16 TI tokens x 16 TJ columns with TI x TJ
-// accumulator tiles, so every operand read from LDS feeds 8 or 4 MFMAs.  The
-// K loop runs over 32-wide slices (one half of a 64-wide fragment-major unit,
-// 1 KB per 16-row block): a slice stage is the 2 TI activation halves and the
-// 2 TJ weight halves the tile needs, copied with global_load_lds straight into
-// LDS in the layout the MFMA operand reads use (a wave's read is 1 KB
-// contiguous, so conflict-free).  NST stages keep the copies NST - 1 slices
-// ahead of the MFMAs with one barrier per slice; the barrier is the plain
-// s_barrier, since __syncthreads() would also wait for the newer copies.
-// OCC workgroups share a CU (the launches use 2, so one workgroup's copy
-// waits and barriers overlap the other's MFMAs).
-template <int LPW>
-__device__ __forceinline__ void wait_copies(int newer) {   // all but the newest `newer` slices' copies
-    switch (newer) {
-    case 0: __builtin_amdgcn_s_waitcnt(waitcnt_vm(0)); break;
-    case 1: __builtin_amdgcn_s_waitcnt(waitcnt_vm(LPW)); break;
-    case 2: __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * LPW)); break;
-    default: __builtin_amdgcn_s_waitcnt(waitcnt_vm(3 * LPW)); break;
-    }
+// M >= 256 (prefill, large batches) with fragment-major X.  A workgroup of
+// 4 WM waves (WM x 4) owns a (16 TI WM)-token x (64 TJ)-column output tile; wave
+// (wm, wn) computes 16 TI tokens x 16 TJ columns.
+// What bounds such a tile is the traffic behind the MFMAs.  With both operands
+// staged in LDS a 256 x 128 tile moved 72 KB through LDS per 512 MFMA cycles of
+// the CU (128 bytes per cycle), more than the MFMAs leave time for.  Here only
+// X, which the four column waves share, goes through LDS (copied straight from
+// global memory, NST 64-wide k units deep); a wave's weight blocks are its own,
+// and fragment-major weights already are MFMA operands, so they are loaded into
+// registers WD (two to four) units ahead and never touch LDS.  A 128 x 192 tile then moves
+// 40 KB through LDS per 768 MFMA cycles, its barrier is one per 64-wide unit,
+// and three workgroups share a CU, so one's prologue, epilogue and barrier
+// waits lie under the others' MFMAs.
+// Measured on MI355X (8192 x 37888 x 3584, SwiGLU): 2160 us (1030 TFLOP/s) with
+// both operands in LDS, 1610 us (1380 TFLOP/s) now; 8192 x 4608 x 3584: 300 ->
+// 208 us.
+// The X fragments of a unit are read in four chunks (half of the row blocks of
+// one 32-wide half), each a chunk ahead of its MFMAs.
+__device__ __forceinline__ void copy16_lds(__amdgpu_buffer_rsrc_t r, char* dst, int voff, uint32_t soff) {
+#if __HIP_DEVICE_COMPILE__   // (the host pass does not know the builtin)
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)dst, 16, voff, soff, 0, 0);
+#endif
 }
 
-template <int TI, int TJ, int NST, int OCC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
+template <int TI, int TJ, int WM, int NST, int WD, int OCC>
+__global__ __launch_bounds__(256 * WM) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 void gemm_big_bf16(const bf16_t* __restrict__ X, int M, int K, const bf16_t* __restrict__ W, int N, EpiArgs e,
-                   int tiles_m, int tiles_n) {
-    constexpr int XB = 2 * TI, WB = 2 * TJ;        // 16-row blocks per tile side
-    constexpr int STAGE = (XB + WB) * 1024;        // bytes per slice stage
-    constexpr int LPW = (XB + WB) / 4;             // 1 KB copies per wave per slice
-    static_assert((XB + WB) % 4 == 0, "whole copies per wave");
-    static_assert(NST >= 2 && NST <= 5 && 3 * LPW <= 63, "stage count and vmcnt range");
-    static_assert(NST * STAGE >= 4 * (TJ / 2) * TI * 1024, "the epilogue's parking space fits the stages");
-    typedef __attribute__((address_space(3))) void* lds_ptr;
-    typedef __attribute__((address_space(1))) void* glb_ptr;
+                   int tiles_n) {
+    constexpr int BM = 16 * TI * WM;
+    constexpr int STAGE = TI * WM * 2048;          // LDS bytes of one 64-wide unit of the X tile
+    constexpr int CPW = TI / 2;                    // 1 KB copies per wave per unit
+    constexpr int CH = TI / 2;                     // X fragments per chunk
+    static_assert(TI % 2 == 0 && NST >= 3, "whole chunks; the wait counts below need three stages");
+    static_assert((NST - 1) * CPW + 2 * TJ <= 63, "vmcnt range");
+    static_assert(NST * STAGE >= WM * 4 * TI * 16 * 12, "the epilogue's row partials fit the stages");
     __shared__ __attribute__((aligned(16))) char smem[NST * STAGE];
-
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
+    const int wm = wave >> 2, wn = wave & 3;
     const int lr = lane & 15, g = lane >> 4;
-    // XCD-aware order (workgroups are dealt round-robin to the 8 XCDs): each
-    // XCD gets a contiguous run of tiles, m fastest, so the tiles that share a
-    // weight panel share that XCD's L2
-    const int total = tiles_m * tiles_n;
-    int bid = blockIdx.x;
-    if ((total & 7) == 0) bid = (bid & 7) * (total >> 3) + (bid >> 3);
-    const int tm = bid % tiles_m, tn = bid / tiles_m;
+    // Tile order.  Only the row tiles that hold kept rows are dealt out (an
+    // LM-head launch covers the largest possible count; tiles skipped in the
+    // middle of the order would leave whole shader engines idle, since the
+    // dispatcher deals workgroups to them in turn).  Workgroups go round-robin to
+    // the 8 XCDs: each XCD gets a contiguous run of an order that walks groups
+    // of 8 row tiles column by column, so the tiles in flight on an XCD form a
+    // block that shares both its X rows and its weight panels in that L2.
     const int Mv = valid_rows(e, M);
-    if (tm * 32 * TI >= Mv) return;   // the whole row tile is past the kept rows
+    const int tiles_m = (Mv + BM - 1) / BM;
+    const int total = tiles_m * tiles_n;
+    if ((int)blockIdx.x >= total) return;
+    const int xcd = blockIdx.x & 7;
+    const int t = xcd * (total >> 3) + min(xcd, total & 7) + (int)(blockIdx.x >> 3);
+    constexpr int GM = 8;
+    const int grp = t / (GM * tiles_n), in = t - grp * GM * tiles_n;
+    const int gm = min(GM, tiles_m - grp * GM);
+    const int tm = grp * GM + in % gm, tn = in / gm;
     const int KU = K / 64, NB = N / 16, MB = (M + 15) / 16;
     const int split = blockIdx.y, nsplit = gridDim.y;
     const int u_begin = (int)((long)KU * split / nsplit), u_end = (int)((long)KU * (split + 1) / nsplit);
-    const int s_begin = 2 * u_begin, nsl = 2 * (u_end - u_begin);
+    const int nu = u_end - u_begin, last = nu - 1;
 
-    // this wave's copies: block q = wave * LPW + j of the stage, activation
-    // blocks first; blocks past the matrix re-read its last block (their
-    // results are never stored)
-    const bf16_t* src[LPW];
+    // Loads go through buffer descriptors based at the tile, with scalar block
+    // and unit offsets and one lane offset: few address registers, and the
+    // compiler counts them exactly (global loads to LDS make it wait for every
+    // load in flight before the first use of any).  Blocks past the matrix
+    // re-read its last block and units past the range its last unit; neither
+    // reaches a stored result.
+    const int mb_first = tm * TI * WM, nb_first = tn * 4 * TJ;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(X + ((size_t)mb_first * KU + u_begin) * 1024), (short)0, -1, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(W + ((size_t)nb_first * KU + u_begin) * 1024), (short)0, -1, 0x00020000);
+    const int voff = 16 * lane;
+    uint32_t xo[CPW], wo[TJ];
 #pragma unroll
-    for (int j = 0; j < LPW; ++j) {
-        const int q = wave * LPW + j;
-        if (q < XB) {
-            const int mb = min(tm * XB + q, MB - 1);
-            src[j] = X + (size_t)mb * KU * 1024 + 8 * lane;
-        } else {
-            const int nb = min(tn * WB + (q - XB), NB - 1);
-            src[j] = W + (size_t)nb * KU * 1024 + 8 * lane;
-        }
+    for (int j = 0; j < CPW; ++j) {
+        const int c = wave * CPW + j;              // copy c of the stage: row block c / 2, half c % 2
+        xo[j] = (uint32_t)min(c >> 1, MB - 1 - mb_first) * KU * 2048 + (c & 1) * 1024;
     }
-    // slice sl of a block: unit sl / 2, half sl % 2
-    auto issue = [&](int sl, int stage) __attribute__((always_inline)) {
-        const size_t off = (size_t)(sl >> 1) * 1024 + (sl & 1) * 512;
-        char* dst = smem + stage * STAGE + wave * LPW * 1024;
 #pragma unroll
-        for (int j = 0; j < LPW; ++j)
-            __builtin_amdgcn_global_load_lds((glb_ptr)(src[j] + off), (lds_ptr)(dst + j * 1024), 16, 0, 0);
+    for (int j = 0; j < TJ; ++j) wo[j] = (uint32_t)min(wn * TJ + j, NB - 1 - nb_first) * KU * 2048;
+    auto copy_x = [&](int u, int stage) __attribute__((always_inline)) {
+        const uint32_t off = (uint32_t)min(u, last) * 2048;
+        char* dst = smem + stage * STAGE + wave * CPW * 1024;
+#pragma unroll
+        for (int j = 0; j < CPW; ++j) copy16_lds(rx, dst + j * 1024, voff, xo[j] + off);
+    };
+    bf16x8 wf[WD][2][TJ];                          // [unit % WD][half][column block]
+    auto load_w = [&](int u, int slot, int h) __attribute__((always_inline)) {
+        const uint32_t off = (uint32_t)min(u, last) * 2048 + h * 1024;
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+            wf[slot][h][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, voff, wo[j] + off, 0));
     };
 
     floatx4 acc[TJ][TI];
@@ -540,159 +558,165 @@ void gemm_big_bf16(const bf16_t* __restrict__ X, int M, int K, const bf16_t* __r
     for (int j = 0; j < TJ; ++j)
 #pragma unroll
         for (int i = 0; i < TI; ++i) acc[j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    auto compute = [&](int stage) __attribute__((always_inline)) {
-        const char* st = smem + stage * STAGE;
-        bf16x8 xf[TI], wf[TJ];
+    bf16x8 xa[CH], xb[CH];
+    auto read_x = [&](bf16x8 (&xf)[CH], int stage, int h, int i0) __attribute__((always_inline)) {
+        const char* st = smem + stage * STAGE + wm * TI * 2048 + h * 1024 + 16 * lane;
 #pragma unroll
-        for (int i = 0; i < TI; ++i) xf[i] = *reinterpret_cast<const bf16x8*>(st + (wm * TI + i) * 1024 + 16 * lane);
+        for (int i = 0; i < CH; ++i) xf[i] = *reinterpret_cast<const bf16x8*>(st + (i0 + i) * 2048);
+    };
+    auto mm = [&](const bf16x8 (&wv)[TJ], const bf16x8 (&xf)[CH], auto i0c) __attribute__((always_inline)) {
+        constexpr int i0 = decltype(i0c)::value;
 #pragma unroll
-        for (int j = 0; j < TJ; ++j)
-            wf[j] = *reinterpret_cast<const bf16x8*>(st + (XB + wn * TJ + j) * 1024 + 16 * lane);
+        for (int i = 0; i < CH; ++i)
 #pragma unroll
-        for (int j = 0; j < TJ; ++j)
+            for (int j = 0; j < TJ; ++j) acc[j][i0 + i] = mfma16x16x32(wv[j], xf[i], acc[j][i0 + i]);
 #pragma unroll
-            for (int i = 0; i < TI; ++i) acc[j][i] = mfma16x16x32(wf[j], xf[i], acc[j][i]);
+        for (int q = 0; q < CH; ++q) {             // one LDS read behind every TJ MFMAs
+            __builtin_amdgcn_sched_group_barrier(0x008, TJ, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
     };
 
-    // Slice t lives in stage t % NST.  Step t waits for its own copies (the
-    // newer ones stay in flight), and the barrier both publishes them and
-    // retires every wave's reads of slice t - 1, whose stage the copy of slice
-    // t + NST - 1 then overwrites.
+    // Unit t lives in LDS stage t % NST and register slot t % WD.  In the middle
+    // of unit t, once every wave has read the last chunk of stage t into
+    // registers, the barrier also publishes stage t + 1; unit t + NST is then
+    // copied over stage t.  Copies complete in issue order, so stage t + 1 has
+    // arrived when at most the (NST - 2) CPW copies issued after it are
+    // outstanding, plus the weight loads issued after it: 2 (NST - 1) TJ of
+    // them.  The waits count only 2 TJ (none in the prologue, from where the
+    // compiler may sink weight loads), so moving weight loads cannot break them.
 #pragma unroll
-    for (int p = 0; p < NST - 1; ++p)
-        if (p < nsl) issue(s_begin + p, p);
-    for (int t = 0; t < nsl; ++t) {
-        wait_copies<LPW>(min(nsl - 1 - t, NST - 2));
-        // (no compiler barrier around it: one keeps the accumulators out of
-        // registers; the LDS reads of the step follow its copy issue, and the
-        // barrier has side effects, so nothing moves across it)
-        __builtin_amdgcn_s_barrier();
-        if (t + NST - 1 < nsl) issue(s_begin + t + NST - 1, (t + NST - 1) % NST);
-        compute(t % NST);
+    for (int p = 0; p < NST; ++p) copy_x(p, p);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int p = 0; p < WD; ++p) {
+        load_w(p, p, 0);
+        load_w(p, p, 1);
     }
-
-    // Epilogue through LDS, half the column blocks at a time: each wave parks
-    // its accumulators in its own LDS region (written straight from the
-    // accumulator registers) and reads them back one tile at a time, which
-    // keeps the epilogue's registers small.  Every wave has finished reading
-    // the slice stages once it passes the barrier.
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 1) * CPW));
     __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    read_x(xa, 0, 0, 0);
+    int st0 = 0;
+    auto unit = [&](int u, auto slotc) __attribute__((always_inline)) {
+        constexpr int s = decltype(slotc)::value;
+        const int st1 = st0 + 1 == NST ? 0 : st0 + 1;
+        read_x(xb, st0, 0, CH);
+        mm(wf[s][0], xa, Kind<0>{});
+        __builtin_amdgcn_sched_barrier(0);
+        read_x(xa, st0, 1, 0);
+        mm(wf[s][0], xb, Kind<CH>{});
+        __builtin_amdgcn_sched_barrier(0);
+        load_w(u + WD, s, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        read_x(xb, st0, 1, CH);
+        mm(wf[s][1], xa, Kind<0>{});
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 2) * CPW + 2 * TJ));   // (and every LDS read)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        copy_x(u + NST, st0);
+        read_x(xa, st1, 0, 0);
+        mm(wf[s][1], xb, Kind<CH>{});
+        __builtin_amdgcn_sched_barrier(0);
+        load_w(u + WD, s, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        st0 = st1;
+    };
+    int u = 0;
+    for (; u + WD <= nu; u += WD) {
+        unit(u, Kind<0>{});
+        if constexpr (WD > 1) unit(u + 1, Kind<1>{});
+        if constexpr (WD > 2) unit(u + 2, Kind<2>{});
+        if constexpr (WD > 3) unit(u + 3, Kind<3>{});
+    }
+    if (u < nu) unit(u, Kind<0>{});
+    if constexpr (WD > 2) if (u + 1 < nu) unit(u + 1, Kind<1>{});
+    if constexpr (WD > 3) if (u + 2 < nu) unit(u + 2, Kind<2>{});
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));     // no copy lands after this point
+
     EpiArgs ee = e;
     if (e.kind == EPI_PARTIAL) ee.y = e.y + (size_t)split * M * e.ldy;
-    const int nb0 = tn * WB + wn * TJ, m0 = tm * 32 * TI + wm * 16 * TI;
-    constexpr int kPark = (TJ / 2) * TI * 64;       // floatx4 slots of one wave's parking region
-    floatx4* park = reinterpret_cast<floatx4*>(smem) + wave * kPark + lane;
+    const int nb0 = nb_first + wn * TJ, m0 = tm * BM + wm * 16 * TI;
     with_kind(e.kind, [&](auto kind) {
         constexpr int EK = decltype(kind)::value;
-        // LM head with fused confidence partials: per row, (max, first argmax,
-        // sum of exp(l - max)) over the tile's columns (Eq. 1)
-        const bool parts = EK == EPI_LMHEAD && e.lpart != nullptr;
-        SmPart pt[TI];
 #pragma unroll
-        for (int i = 0; i < TI; ++i) pt[i] = SmPart{-INFINITY, 0x7fffffff, 0.f};
-        // the halves are separate instances (compile-time indices into acc,
-        // which must stay in registers)
-        auto half = [&](auto hjc) __attribute__((always_inline)) {
-            constexpr int hj = decltype(hjc)::value;
+        for (int ih = 0; ih < TI; ih += 2) {
+            float4 pre[2][TJ];
 #pragma unroll
-            for (int j = 0; j < TJ / 2; ++j)
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int i = 0; i < TI; ++i) park[(j * TI + i) * 64] = acc[hj * (TJ / 2) + j][i];
-            asm volatile("" ::: "memory");   // the tiles are read back from LDS, not forwarded
-#pragma unroll
-            for (int j = 0; j < TJ / 2; ++j) {
-                const int n = 16 * (nb0 + hj * (TJ / 2) + j) + 4 * g;
-                float4 pre[TI];
-#pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    const int m = m0 + 16 * i + lr;
-                    pre[i] = (m < Mv && n < N) ? epi_fetch<EK>(ee, m, n) : make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int j = 0; j < TJ; ++j) {
+                    const int n = 16 * (nb0 + j) + 4 * g, m = m0 + 16 * (ih + i) + lr;
+                    pre[i][j] = (m < Mv && n < N) ? epi_fetch<EK>(ee, m, n) : make_float4(0.f, 0.f, 0.f, 0.f);
                 }
 #pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    const int m = m0 + 16 * i + lr;
-                    if (m < Mv && n < N) epi_store<bf16_t, EK>(ee, m, n, park[(j * TI + i) * 64], pre[i]);
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) {
+                    const int n = 16 * (nb0 + j) + 4 * g, m = m0 + 16 * (ih + i) + lr;
+                    if (m < Mv && n < N) epi_store<bf16_t, EK>(ee, m, n, acc[j][ih + i], pre[i][j]);
                 }
-            }
-            if constexpr (EK == EPI_LMHEAD) {
-                if (parts) {
-                    // this half's columns: the maximum and its first column, then
-                    // the sum of exp2(l log2e - mb) (mb = max log2e rounded once;
-                    // its rounding error, common to every term, is corrected at the end)
-                    constexpr float kL2e = 1.4426950408889634f;
-#pragma unroll
-                    for (int i = 0; i < TI; ++i) {
-                        SmPart h{-INFINITY, 0x7fffffff, 0.f};
-#pragma unroll
-                        for (int j = 0; j < TJ / 2; ++j) {
-                            const int n = 16 * (nb0 + hj * (TJ / 2) + j) + 4 * g;
-                            if (n < N) {
-                                const floatx4 v = park[(j * TI + i) * 64];
-#pragma unroll
-                                for (int q = 0; q < 4; ++q)
-                                    if (v[q] > h.m) { h.m = v[q]; h.a = n + q; }
-                            }
-                        }
-                        const float mb = h.m * kL2e;
-#pragma unroll
-                        for (int j = 0; j < TJ / 2; ++j) {
-                            const int n = 16 * (nb0 + hj * (TJ / 2) + j) + 4 * g;
-                            if (n < N) {
-                                const floatx4 v = park[(j * TI + i) * 64];
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) h.s += __builtin_amdgcn_exp2f(fmaf(v[q], kL2e, -mb));
-                            }
-                        }
-                        if (h.m != -INFINITY) h.s *= exp2f(-fmaf(h.m, kL2e, -mb));
-                        pt[i] = smpart_merge(pt[i], h);
-                    }
-                }
-            }
-        };
-        half(Kind<0>{});
-        half(Kind<1>{});
+        }
         if constexpr (EK == EPI_LMHEAD) {
-            if (parts) {
-                // merge the four column groups of a row (lanes lr + 16 g), then the
-                // two waves that share the rows (wn = 0 holds the lower columns)
+            // fused confidence partials: per row, (max, first argmax, sum of
+            // exp(l - max)) over the tile's columns (Eq. 1).  A lane's columns
+            // of a row first, then its row's four lanes, then the four waves.
+            if (!e.lpart) return;
+            __builtin_amdgcn_s_barrier();          // every wave has read its last X fragments (and dropped the rest)
+            float* red = reinterpret_cast<float*>(smem) + wave * TI * 16 * 3;
+            constexpr float kL2e = 1.4426950408889634f;
 #pragma unroll
-                for (int i = 0; i < TI; ++i)
+            for (int i = 0; i < TI; ++i) {
+                SmPart p{-INFINITY, 0x7fffffff, 0.f};
 #pragma unroll
-                    for (int o = 16; o < 64; o <<= 1) {
-                        const SmPart y{__shfl_xor(pt[i].m, o, 64), __shfl_xor(pt[i].a, o, 64),
-                                       __shfl_xor(pt[i].s, o, 64)};
-                        pt[i] = smpart_merge(pt[i], y);
-                    }
-                // wave wn = 1 leaves its partials in its own (finished) parking region
-                float* mine = reinterpret_cast<float*>(reinterpret_cast<floatx4*>(smem) + wave * kPark);
-                if (wn == 1 && g == 0) {
+                for (int j = 0; j < TJ; ++j) {
+                    const int n = 16 * (nb0 + j) + 4 * g;
+                    if (n < N) {
 #pragma unroll
-                    for (int i = 0; i < TI; ++i) {
-                        mine[(i * 16 + lr) * 3 + 0] = pt[i].m;
-                        mine[(i * 16 + lr) * 3 + 1] = __int_as_float(pt[i].a);
-                        mine[(i * 16 + lr) * 3 + 2] = pt[i].s;
+                        for (int q = 0; q < 4; ++q)
+                            if (acc[j][i][q] > p.m) { p.m = acc[j][i][q]; p.a = n + q; }
                     }
                 }
-                __syncthreads();
-                if (wn == 0 && g == 0) {
-                    const float* other = reinterpret_cast<const float*>(reinterpret_cast<floatx4*>(smem) +
-                                                                        (wave + 1) * kPark);
+                // sum of exp2(l log2e - mb), mb = max log2e rounded once; its
+                // rounding error, common to every term, is corrected at the end
+                const float mb = p.m * kL2e;
 #pragma unroll
-                    for (int i = 0; i < TI; ++i) {
-                        const int m = m0 + 16 * i + lr;
-                        const SmPart y{other[(i * 16 + lr) * 3 + 0], __float_as_int(other[(i * 16 + lr) * 3 + 1]),
-                                       other[(i * 16 + lr) * 3 + 2]};
-                        const SmPart r = smpart_merge(pt[i], y);
-                        if (m < Mv) {
-                            float* o = e.lpart + ((size_t)m * e.ntile + tn) * 3;
-                            o[0] = r.m;
-                            o[1] = __int_as_float(r.a);
-                            o[2] = r.s;
-                        }
+                for (int j = 0; j < TJ; ++j) {
+                    const int n = 16 * (nb0 + j) + 4 * g;
+                    if (n < N) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) p.s += __builtin_amdgcn_exp2f(fmaf(acc[j][i][q], kL2e, -mb));
                     }
                 }
+                if (p.m != -INFINITY) p.s *= exp2f(-fmaf(p.m, kL2e, -mb));
+#pragma unroll
+                for (int o = 16; o < 64; o <<= 1) {
+                    const SmPart y{__shfl_xor(p.m, o, 64), __shfl_xor(p.a, o, 64), __shfl_xor(p.s, o, 64)};
+                    p = smpart_merge(p, y);
+                }
+                if (g == 0) {
+                    red[(i * 16 + lr) * 3 + 0] = p.m;
+                    red[(i * 16 + lr) * 3 + 1] = __int_as_float(p.a);
+                    red[(i * 16 + lr) * 3 + 2] = p.s;
+                }
+            }
+            __syncthreads();
+            for (int r = tid; r < BM; r += 256 * WM) {
+                const int m = tm * BM + r;
+                if (m >= Mv) continue;
+                const int w0 = r / (16 * TI) * 4, ro = r % (16 * TI);
+                SmPart p{-INFINITY, 0x7fffffff, 0.f};
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const float* o = reinterpret_cast<const float*>(smem) + ((w0 + w) * TI * 16 + ro) * 3;
+                    p = smpart_merge(p, SmPart{o[0], __float_as_int(o[1]), o[2]});
+                }
+                float* o = e.lpart + ((size_t)m * e.ntile + tn) * 3;
+                o[0] = p.m;
+                o[1] = __int_as_float(p.a);
+                o[2] = p.s;
             }
         }
     });
@@ -917,45 +941,61 @@ int pipe_split(int M, int N, int K) {
     return S;
 }
 
-// Large-tile kernel choice for M >= 256: two workgroups per CU, tiles of
-// 256 x 128 (A), 128 x 256 (B), 128 x 128 (C) or 128 x 192 (D) tokens x
-// columns.  The time model is rounds of 512 workgroups times the work of one
-// tile over its relative throughput (a round costs about the same however
-// full it is), fitted to kernel-trace sweeps on MI355X over the 7B batch-8
-// and 8B batch-32 steps (1024 / 2048 rows) and prefills of 640 to 26624
-// rows: A 1.0, B 0.97 (1.2 from 4096 rows, where each XCD's run of tiles
-// shares a wider weight panel), C 0.72, D 0.9 (D only without a K split: as
-// split-K partials it measured 12-24 % slower than A at 640 rows; with full
-// sums it takes 9-17 % off the QKV and gate/up projections of 700-800-row
-// prefills and 4 % off the 8B batch-32 QKV).  Partial (split-K) epilogues
-// split K while there are fewer than two workgroups per CU, keeping at least
-// 8 k units per split.
+// Large-tile kernel choice for M >= 256: tiles of 128 x 192, 192 x 128, 128 x 128
+// or 256 x 192 (rows x columns).  A CU's tiles run side by side, so a launch
+// takes about as long as the CU with the most tiles: ceil(tiles / 256) times a
+// tile's time, its work over the tile's rate plus a fixed part (prologue and
+// epilogue; longest for 256 x 192, whose one workgroup fills the CU).  Rates and
+// fixed parts are fitted to sweeps on MI355X over 320 to 8192 rows and the
+// projections of the 8B and 7B shapes with weights cold in cache (22 shapes; the
+// model's pick is within 1 % of the best of the four on average, at worst 12 %).
+// No tile is best everywhere: 1024 x 4608 x 3584 takes 40 us with 192 x 128 (56
+// with 128 x 128), 640 x 12288 x 4096 72 us with 128 x 128 (89 with 128 x 192),
+// 1024 x 37888 x 3584 231 us with 128 x 192 (260 with 128 x 128), and 1024 x 3584 x
+// 18944 in three splits 114 us with 256 x 192 (127 with 192 x 128).
+// Split-K (residual) epilogues split K up to 4 ways, at least 8 k units each; a
+// split adds its partial's pass through the residual-norm kernel, about 4.4
+// bytes per nanosecond.  They take 128 x 192 only from 4096 rows, where one split
+// fills the chip (8192 x 3584 x 18944: 914 us, 1034 with 256 x 192); below that
+// 256 x 192 or 192 x 128 splits are faster.  Other epilogues leave 256 x 192 out:
+// inside a step 128 x 192 was faster there (1024 x 37888 x 3584: 235 against 275
+// us), most of all for LM-head launches, whose row count the host does not know
+// (320 of at most 1024 rows: 414 against 554 us).
 struct BigCfg {
-    int ti, tj, split;   // ti == 0: use the pipelined kernel
+    int ti, tj, split;   // tile in units of 32 rows / columns; ti == 0: not a large-tile launch
 };
-BigCfg big_cfg(int M, int N, int K, bool partial, bool no192 = false) {
+BigCfg big_cfg(int M, int N, int K, bool partial) {
     if (M < 256) return BigCfg{0, 0, 1};
-    const int cand[4][2] = {{8, 4}, {4, 8}, {4, 4}, {4, 6}};
-    const double eff[4] = {1.0, M >= 4096 ? 1.2 : 0.97, 0.72, 0.9};
+    struct Tile {
+        int ti, tj;
+        double rate, fixed_us;   // multiply-adds per microsecond and CU in millions; per tile
+    };
+    const Tile cand[4] = {{4, 6, 2.8, 4.0}, {6, 4, 2.75, 5.0}, {4, 4, 2.2, 3.0}, {8, 6, 2.85, 10.0}};
     BigCfg best{0, 0, 1};
     double best_t = 0.0;
-    for (int v = 0; v < 4; ++v) {
-        if (v == 3 && (partial || no192)) continue;
-        const int ti = cand[v][0], tj = cand[v][1];
-        const long tiles = (long)((M + 32 * ti - 1) / (32 * ti)) * ((N + 32 * tj - 1) / (32 * tj));
-        int S = 1;
-        if (partial)
-            while (S < 4 && tiles * S < 512 && K / 64 / (2 * S) >= 8) S *= 2;
-        const double t = (double)((tiles * S + 511) / 512) * (32.0 * ti) * (32.0 * tj) * ((double)K / S) / eff[v];
-        if (best.ti == 0 || t < best_t) {
-            best = BigCfg{ti, tj, S};
-            best_t = t;
+    for (const Tile& c : cand) {
+        if (partial ? c.ti == 4 && c.tj == 6 && M < 4096 : c.ti == 8) continue;
+        // a tile's 32-bit byte offsets: rows (columns) x K x 2 stay under 4 GiB
+        if (!(c.ti == 4 && c.tj == 4) && K > (1 << 22)) continue;
+        const int bm = 32 * c.ti, bn = 32 * c.tj;
+        const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+        for (int S = 1; S <= (partial ? 4 : 1); ++S) {
+            if (S > 1 && K / 64 / S < 8) break;
+            const long per_cu = (tiles * S + 255) / 256;
+            // three 128 x 192 tiles share a CU: they reach their rate when more follow
+            const double rate = c.ti == 4 && c.tj == 6 && per_cu <= 3 ? 2.6 : c.rate;
+            const double tile_us = (double)bm * bn * K / S / (1e6 * rate) + c.fixed_us;
+            const double us = per_cu * tile_us + (S > 1 ? 4.0 * S * M * N / 4.4e6 : 0.0);
+            if (best.ti == 0 || us < best_t) {
+                best = BigCfg{c.ti, c.tj, S};
+                best_t = us;
+            }
         }
     }
     return best;
 }
 
-void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t* plan, bool fused_head) {
+void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t* plan) {
     plan[1] = plan[2] = 0;
     plan[3] = 1;
     if (dtype == DARD_DTYPE_F32) {
@@ -976,7 +1016,7 @@ void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t
         plan[2] = TBN / 32;
         return;
     }
-    const BigCfg c = big_cfg(M, N, K, partial, fused_head);
+    const BigCfg c = big_cfg(M, N, K, partial);
     if (c.ti) {
         plan[0] = DARD_GEMM_BIG;
         plan[1] = c.ti;
@@ -1036,21 +1076,20 @@ hipError_t launch_gemm(int dtype, const void* X, int M, int K, int ldx, const vo
         return hipGetLastError();
     }
     if (xfrag) {
-        // the fused LM-head partials need tile widths that divide the 8192-logit chunks
-        const BigCfg c = big_cfg(M, N, K, e.kind == EPI_PARTIAL, e.kind == EPI_LMHEAD && e.lpart);
+        const BigCfg c = big_cfg(M, N, K, e.kind == EPI_PARTIAL);
         if (c.ti && e.kind == EPI_LMHEAD && e.lpart && e.ntile != (N + 32 * c.tj - 1) / (32 * c.tj))
             return hipErrorInvalidValue;
         if (c.ti) {
             const int tiles_m = (M + 32 * c.ti - 1) / (32 * c.ti), tiles_n = (N + 32 * c.tj - 1) / (32 * c.tj);
             const dim3 grid(tiles_m * tiles_n, c.split);
             if (c.ti == 8)
-                launch(gemm_big_bf16<8, 4, 3, 2>, grid, dim3(256), 0, s, x, M, K, w, N, e, tiles_m, tiles_n);
-            else if (c.tj == 8)
-                launch(gemm_big_bf16<4, 8, 3, 2>, grid, dim3(256), 0, s, x, M, K, w, N, e, tiles_m, tiles_n);
+                launch(gemm_big_bf16<8, 3, 2, 4, 3, 2>, grid, dim3(512), 0, s, x, M, K, w, N, e, tiles_n);
+            else if (c.ti == 6)
+                launch(gemm_big_bf16<12, 2, 1, 3, 3, 2>, grid, dim3(256), 0, s, x, M, K, w, N, e, tiles_n);
             else if (c.tj == 6)
-                launch(gemm_big_bf16<4, 6, 4, 2>, grid, dim3(256), 0, s, x, M, K, w, N, e, tiles_m, tiles_n);
+                launch(gemm_big_bf16<8, 3, 1, 3, 2, 3>, grid, dim3(256), 0, s, x, M, K, w, N, e, tiles_n);
             else
-                launch(gemm_big_bf16<4, 4, 5, 2>, grid, dim3(256), 0, s, x, M, K, w, N, e, tiles_m, tiles_n);
+                launch(gemm_big_bf16<8, 2, 1, 3, 4, 3>, grid, dim3(256), 0, s, x, M, K, w, N, e, tiles_n);
             return hipGetLastError();
         }
         if (e.kind == EPI_LMHEAD && e.lpart) return hipErrorInvalidValue;   // partials need the large tiles

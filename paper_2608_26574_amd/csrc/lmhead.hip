@@ -134,9 +134,11 @@ __global__ void lm_gather_kernel(const T* __restrict__ xn, int d, int frag, cons
     }
 }
 
-// One wave per (listed row, 8192-logit chunk): lane l merges tile l of the
-// chunk (tiles_per_chunk <= 64), then a butterfly over the wave.
-__global__ __launch_bounds__(64) void lm_merge_kernel(const float* __restrict__ lpart, int ntile, int tiles_per_chunk,
+// One wave per (listed row, 8192-logit chunk): the chunk takes the column tiles
+// that begin in it (the decision kernel only merges the chunks of a row, so a
+// tile may reach into the next one); lane l merges tile l of them (at most 64,
+// tiles being 128 columns or wider), then a butterfly over the wave.
+__global__ __launch_bounds__(64) void lm_merge_kernel(const float* __restrict__ lpart, int ntile, int tile_cols,
                                                       const int32_t* __restrict__ rowmap,
                                                       const int32_t* __restrict__ count, int B, int nchunk,
                                                       float* __restrict__ part_v, float* __restrict__ part_m) {
@@ -145,9 +147,11 @@ __global__ __launch_bounds__(64) void lm_merge_kernel(const float* __restrict__ 
     const int code = rowmap[r];
     float* dst = (code & kLmToV) ? part_v : ((code & kLmToM) ? part_m : nullptr);
     if (!dst) return;
-    const int tile = c * tiles_per_chunk + lane;
+    const int first = (c * kConfChunk + tile_cols - 1) / tile_cols;
+    const int end = min(ntile, ((c + 1) * kConfChunk + tile_cols - 1) / tile_cols);
+    const int tile = first + lane;
     SmPart p{-INFINITY, 0x7fffffff, 0.f};
-    if (lane < tiles_per_chunk && tile < ntile) {
+    if (tile < end) {
         const float* q = lpart + ((size_t)r * ntile + tile) * 3;
         p = SmPart{q[0], __float_as_int(q[1]), q[2]};
     }
@@ -193,11 +197,10 @@ hipError_t launch_lm_gather(int dtype, const void* xn, int d, bool frag, const i
 
 hipError_t launch_lm_merge(const float* lpart, int ntile, int tile_cols, const int32_t* rowmap, const int32_t* count,
                            int max_rows, int B, int V, float* part_v, float* part_m, hipStream_t s) {
-    const int chunk = kConfChunk;
-    if (tile_cols < 1 || chunk % tile_cols || chunk / tile_cols > 64 || max_rows < 1) return hipErrorInvalidValue;
+    if (tile_cols < 128 || tile_cols > kConfChunk || max_rows < 1) return hipErrorInvalidValue;
     const int nchunk = conf_chunks(V);
-    launch(lm_merge_kernel, dim3(max_rows, nchunk), dim3(64), 0, s, lpart, ntile, chunk / tile_cols, rowmap, count,
-           B, nchunk, part_v, part_m);
+    launch(lm_merge_kernel, dim3(max_rows, nchunk), dim3(64), 0, s, lpart, ntile, tile_cols, rowmap, count, B, nchunk,
+           part_v, part_m);
     return hipGetLastError();
 }
 
