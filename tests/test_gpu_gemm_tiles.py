@@ -61,7 +61,7 @@ def test_prefill_tilings(b, P, d, F, gu, down):
     print("[case] prefill tilings", b, P, d, F, gu, down, file=sys.stderr, flush=True)
     assert tuple(dard.dard_gemm_plan(b * P, 2 * F, d)) == gu
     assert tuple(dard.dard_gemm_plan(b * P, d, F, partial=True)) == down
-    dims = synth.Dims(2, d, d // 128, max(1, d // 256), 128, F, 1040, 2048, "bf16")
+    dims = synth.Dims(2, d, d // 128, max(1, d // 256), 128, F, 1040, 4096, "bf16")
     w = synth.make_weights(dims, seed=5, device="cuda")
     ids = torch.from_numpy(synth.prompt_ids(b, P, dims.vocab, seed=6)).cuda()
     eng = dard.Engine(dims, w, b, 8, P + 16)
