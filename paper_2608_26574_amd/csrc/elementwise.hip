@@ -8,40 +8,49 @@ namespace dard {
 
 namespace {
 
-__device__ __forceinline__ float block_sum(float v, float* red) {
-    v = wave_sum(v);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    float t = 0.f;
-    const int nw = blockDim.x >> 6;
-    for (int i = 0; i < nw; ++i) t += red[i];
-    __syncthreads();
-    return t;
-}
-
 // Offset of element (row, c) of a [rows][d] activation, row-major or fragment-major.
 __device__ __forceinline__ size_t act_off(int row, int c, int d, bool frag) {
     return frag ? frag_off(row, c, d) : (size_t)row * d + c;
 }
 
-// xn[row] = h / sqrt(mean(h^2) + eps) * gain, rounded to T.
-template <typename T>
-__device__ void norm_row(const float* h, const T* gain, int d, float eps, T* xn, int row, bool frag, float* red) {
-    float ss = 0.f;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) ss += h[c] * h[c];
-    ss = block_sum(ss, red);
-    const float inv = rsqrtf(ss / (float)d + eps);
-    for (int c = threadIdx.x; c < d; c += blockDim.x)
-        St<T>::st(xn + act_off(row, c, d, frag), h[c] * inv * St<T>::ld(gain + c));
+// N consecutive values (16 bytes of T, aligned) as floats, and back.
+template <typename T, int N>
+__device__ __forceinline__ void load_vec(const T* p, float (&v)[N]) {
+    static_assert(N * sizeof(T) == 16 || N * sizeof(T) == 8, "one 8- or 16-byte access");
+    typedef T Vec __attribute__((ext_vector_type(N)));
+    const Vec x = *reinterpret_cast<const Vec*>(p);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const T e = x[i];
+        v[i] = St<T>::ld(&e);
+    }
+}
+template <typename T, int N>
+__device__ __forceinline__ void store_vec(T* p, const float (&v)[N]) {
+    typedef T Vec __attribute__((ext_vector_type(N)));
+    Vec x;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        T e;
+        St<T>::st(&e, v[i]);
+        x[i] = e;
+    }
+    *reinterpret_cast<Vec*>(p) = x;
 }
 
+// The embedding row is held in registers between its load, the store to h and
+// the normalised store, in 16-byte pieces (an 8-element group of the
+// fragment-major layout is contiguous), so the row costs one read and two
+// writes: 64 rows of 4096 in 5.2 us, 640 rows in 10.6 us (15 and 27 us when h
+// was read back and values were stored one by one).
 template <typename T>
 __global__ __launch_bounds__(256) void embed_norm_kernel(const int32_t* __restrict__ ids, const T* __restrict__ embeds,
                                                          const T* __restrict__ table, const T* __restrict__ gain,
                                                          int d, int vocab, float eps, int step_B, int mask_id,
-                                                         float* __restrict__ h, T* __restrict__ xn, int frag) {
-    __shared__ float red[8];
+                                                         float* __restrict__ h, T* __restrict__ xn, int frag,
+                                                         int embeds_aligned) {
+    constexpr int N = 16 / sizeof(T), kIt = 8192 / (256 * N);   // d <= 8192, a multiple of N
+    __shared__ float red[4];
     const size_t row = blockIdx.x;
     int id;
     if (step_B > 0) {
@@ -53,10 +62,51 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const int32_t* __restri
     // ids are device data: keep every read inside its table
     if (id >= vocab || (id < 0 && embeds == nullptr)) id = id < 0 ? 0 : vocab - 1;
     const T* src = id >= 0 ? table + (size_t)id * d : embeds + row * d;
+    float v[kIt][N];
+    if (id >= 0 || embeds_aligned) {
+#pragma unroll
+        for (int q = 0; q < kIt; ++q) {
+            const int c = (threadIdx.x + 256 * q) * N;
+            if (c < d) load_vec<T, N>(src + c, v[q]);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < kIt; ++q) {
+            const int c = (threadIdx.x + 256 * q) * N;
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                if (c < d) v[q][i] = St<T>::ld(src + c + i);
+        }
+    }
+    float ss = 0.f;
     float* hr = h + row * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) hr[c] = St<T>::ld(src + c);
+#pragma unroll
+    for (int q = 0; q < kIt; ++q) {
+        const int c = (threadIdx.x + 256 * q) * N;
+        if (c < d) {
+#pragma unroll
+            for (int i = 0; i < N; i += 4) {
+                *reinterpret_cast<float4*>(hr + c + i) = make_float4(v[q][i], v[q][i + 1], v[q][i + 2], v[q][i + 3]);
+                ss += v[q][i] * v[q][i] + v[q][i + 1] * v[q][i + 1] + v[q][i + 2] * v[q][i + 2] +
+                      v[q][i + 3] * v[q][i + 3];
+            }
+        }
+    }
+    ss = wave_sum(ss);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
     __syncthreads();
-    norm_row<T>(hr, gain, d, eps, xn, (int)row, frag != 0, red);
+    const float inv = rsqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
+#pragma unroll
+    for (int q = 0; q < kIt; ++q) {
+        const int c = (threadIdx.x + 256 * q) * N;
+        if (c < d) {
+            float gn[N];
+            load_vec<T, N>(gain + c, gn);
+#pragma unroll
+            for (int i = 0; i < N; ++i) gn[i] *= v[q][i] * inv;
+            store_vec<T, N>(xn + act_off((int)row, c, d, frag != 0), gn);
+        }
+    }
 }
 
 // h[row] += sum_s part[s][row] (split-K partials of the preceding projection,
@@ -108,11 +158,10 @@ __global__ __launch_bounds__(512) void resid_norm_kernel(float* __restrict__ h, 
         const int c4 = threadIdx.x + 512 * q;
         if (c4 < n4) {
             const int c = 4 * c4;   // c..c+3 stay inside one 8-element group of the fragment layout
-            T* out = xn + act_off((int)row, c, d, frag != 0);
-            St<T>::st(out, v[q].x * inv * St<T>::ld(gain + c));
-            St<T>::st(out + 1, v[q].y * inv * St<T>::ld(gain + c + 1));
-            St<T>::st(out + 2, v[q].z * inv * St<T>::ld(gain + c + 2));
-            St<T>::st(out + 3, v[q].w * inv * St<T>::ld(gain + c + 3));
+            float gn[4];
+            load_vec<T, 4>(gain + c, gn);
+            const float o[4] = {v[q].x * inv * gn[0], v[q].y * inv * gn[1], v[q].z * inv * gn[2], v[q].w * inv * gn[3]};
+            store_vec<T, 4>(xn + act_off((int)row, c, d, frag != 0), o);
         }
     }
 }
@@ -157,13 +206,16 @@ hipError_t launch_embed_norm(int dtype, const int32_t* ids, const void* embeds, 
                              int mask_id, float* h, void* xn, bool frag, hipStream_t s) {
     TraceScope ts(DARD_K_NORM, s);
     if (frag && !frag_rows(dtype, rows)) return hipErrorInvalidValue;
+    if (d > 8192 || d % (dtype == DARD_DTYPE_BF16 ? 8 : 4)) return hipErrorInvalidValue;
+    const int aligned = (reinterpret_cast<uintptr_t>(embeds) & 15) == 0;
     if (dtype == DARD_DTYPE_BF16)
         launch(embed_norm_kernel<bf16_t>, dim3(rows), dim3(256), 0, s, ids,
                            (const bf16_t*)embeds, (const bf16_t*)table, (const bf16_t*)gain, d, vocab, eps, step_B,
-                           mask_id, h, (bf16_t*)xn, (int)frag);
+                           mask_id, h, (bf16_t*)xn, (int)frag, aligned);
     else
         launch(embed_norm_kernel<float>, dim3(rows), dim3(256), 0, s, ids, (const float*)embeds,
-                           (const float*)table, (const float*)gain, d, vocab, eps, step_B, mask_id, h, (float*)xn, 0);
+                           (const float*)table, (const float*)gain, d, vocab, eps, step_B, mask_id, h, (float*)xn, 0,
+                           aligned);
     return hipGetLastError();
 }
 
