@@ -57,8 +57,8 @@ int check_dims(const dard_dims* d) {
         return fail(DARD_ERR_SHAPE, "bf16 needs d_model, ffn_dim %% 64 == 0 and vocab %% 16 == 0");
     if (d->d_model > 8192) return fail(DARD_ERR_SHAPE, "d_model must be <= 8192");
     if (d->dtype == DARD_DTYPE_BF16) {
-        // the pipelined GEMM (65-255 rows) addresses a weight matrix through a
-        // buffer descriptor: 32-bit byte offsets, so every matrix stays under 4 GiB
+        // the tiled GEMM addresses a tile's weights by 32-bit byte offsets (the
+        // limit is on the whole matrix)
         const size_t D = d->d_model, F = d->ffn_dim, V = d->vocab;
         const size_t qkv = (size_t)(d->n_heads + 2 * d->n_kv_heads) * d->head_dim;
         size_t most = V * D;
@@ -146,9 +146,10 @@ WsLayout ws_layout(const dard_dims* d, int b, int B, int cap) {
     W.w = o; o = align256(o + (size_t)b * B * 4);
     W.ids = o; o = align256(o + rows * 4);          // full-sequence mode: row token ids
     W.tok = o; o = align256(o + (size_t)b * B * 4);   // and the current block's tokens
-    // split-K partials of the O and down projections: up to 8 splits of 64
-    // rows (streaming GEMM) or 4 splits of all rows (pipelined and large-tile GEMMs)
-    const size_t prow = rows * 4 > 8 * 64 ? rows * 4 : 8 * 64;
+    // split-K partials of the O and down projections: up to 4 splits of all
+    // rows, up to 8 below 256 rows
+    const size_t few = rows < 256 ? rows : 256;
+    const size_t prow = rows * 4 > 8 * few ? rows * 4 : 8 * few;
     W.gpart = o; o = align256(o + prow * d->d_model * 4);
     // listed LM-head rows: the compact input (whole 64-row blocks), two row
     // lists, their device counts, and the fused column-tile partials (tiles of
@@ -688,7 +689,7 @@ int step_tail(const Fwd& f, const dard_params* params, int b, int B, const void*
 
     const int max_rows = hidden ? b * B : rows;
     int32_t plan[4];
-    gemm_plan(dt, max_rows, V, D, false, frag, plan);
+    gemm_plan(dt, max_rows, V, D, false, frag, plan, true);
     if (!hidden && plan[0] == DARD_GEMM_STREAM) {
         EpiArgs e{};
         e.kind = EPI_STORE_F32; e.y = logits; e.ldy = V;

@@ -22,10 +22,8 @@
 //     summed in LDS in a fixed order; DEPTH units per wave are in flight in a
 //     register ring.  Weights are read with non-temporal loads (streamed once).
 //     Optional split of K across SPLIT workgroups writes fp32 partials.
-//   gemm_pipe: 64 < M < 256 with fragment-major X, 128 x 128 tiles through a
-//     register ring and an LDS double buffer.
-//   gemm_big: M >= 256 with fragment-major X (prefill, large batches), tiles of
-//     128 x 192 and others, X through LDS, the weights straight to registers.
+//   gemm_big: M > 64 with fragment-major X, tiles of 64 x 64 to 256 x 192, X
+//     through LDS, the weights straight to registers.
 //   gemm_tiled: row-major X (dard_linear), 128 x 128 tiles through LDS.
 #include "common.h"
 #include "launch.h"
@@ -302,161 +300,8 @@ __global__ __launch_bounds__(64 * KSPLIT) void gemm_stream_bf16(const bf16_t* __
     });
 }
 
-// ---------------------------------------------------------------- pipelined tiles
-// M > 64 (prefill, large batches) with fragment-major X.  A workgroup owns a
-// 128-token x (32 WN)-column output tile; wave (wm, wn) computes tokens
-// 64wm..64wm+63 x 16 WN columns with WN x 4 accumulator tiles.  Per 64-wide k
-// unit the workgroup copies the 2 WN weight blocks and 8 activation blocks it
-// needs (both fragment-major, so every 16-byte chunk is a plain copy) into one
-// of two LDS stages; each thread holds its chunks of the next two units in a
-// register ring, so global loads run two units ahead of the MFMAs and one
-// barrier per unit separates the stages.  An optional split of K across
-// workgroups writes fp32 partials (EPI_PARTIAL).
-constexpr int PBM = 128;
-
-template <int WN>
-struct PipeTile {
-    static constexpr int BN = 32 * WN;              // output columns per workgroup
-    static constexpr int CHW = BN / 16 * 128;       // 16-byte weight chunks per stage
-    static constexpr int CHX = PBM / 16 * 128;      // activation chunks per stage
-    static constexpr int CH = CHW + CHX;
-    static constexpr int PER = CH / 256;            // chunks per thread per unit
-};
-
-template <int WN>
-__global__ __launch_bounds__(256, WN <= 4 ? 2 : 1) void gemm_pipe_bf16(const bf16_t* __restrict__ X, int M, int K,
-                                                      const bf16_t* __restrict__ W, int N, EpiArgs e,
-                                                      int tiles_m, int tiles_n) {
-    using T = PipeTile<WN>;
-    __shared__ bf16x8 lds[2][T::CH];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-    const int lr = lane & 15, g = lane >> 4;
-    // XCD-aware order (workgroups are dealt round-robin to the 8 XCDs): each
-    // XCD gets a contiguous run of tiles, m fastest, so tiles sharing a weight
-    // panel share that XCD's L2
-    const int total = tiles_m * tiles_n;
-    int bid = blockIdx.x;
-    if ((total & 7) == 0) bid = (bid & 7) * (total >> 3) + (bid >> 3);
-    const int tm = bid % tiles_m, tn = bid / tiles_m;
-    const int Mv = valid_rows(e, M);
-    if (tm * PBM >= Mv) return;   // the whole row tile is past the kept rows
-    const int KU = K / 64, NB = N / 16, MB = (M + 15) / 16;
-    const int split = blockIdx.y, nsplit = gridDim.y;
-    const int u_begin = (int)((long)KU * split / nsplit), u_end = (int)((long)KU * (split + 1) / nsplit);
-    const int nu = u_end - u_begin;
-
-    // this thread's chunks: c = tid + 256 i; c < CHW: weight block c / 128 of
-    // the tile, else activation block (c - CHW) / 128; blocks past the matrix
-    // re-read its last block (their results are never stored)
-    // Loads go through buffer descriptors (base and size in scalar registers,
-    // 32-bit byte offsets per lane; the hardware returns 0 past the size).
-    static_assert(T::CHW % 256 == 0, "a thread's chunks are all weight or all activation");
-    // (the library rejects bf16 weight matrices of 4 GiB or more, so the byte
-    // counts fit the descriptors' 32-bit record field)
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)W, (short)0, (int)(uint32_t)((size_t)NB * KU * 2048), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)X, (short)0, (int)(uint32_t)((size_t)MB * KU * 2048), 0x00020000);
-    uint32_t off[T::PER];
-#pragma unroll
-    for (int i = 0; i < T::PER; ++i) {
-        const int c = tid + 256 * i;
-        if (i < T::CHW / 256) {
-            const int nb = min(tn * (T::BN / 16) + c / 128, NB - 1);
-            off[i] = ((uint32_t)nb * KU * 1024 + (c & 127) * 8) * 2;
-        } else {
-            const int mb = min(tm * (PBM / 16) + (c - T::CHW) / 128, MB - 1);
-            off[i] = ((uint32_t)mb * KU * 1024 + (c & 127) * 8) * 2;
-        }
-    }
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    bf16x8 ring[2][T::PER];
-    auto gload = [&](int slot, int u) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < T::PER; ++i) {
-            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(i < T::CHW / 256 ? rw : rx,
-                                                                  off[i] + (uint32_t)u * 2048, 0, 0);
-            ring[slot][i] = __builtin_bit_cast(bf16x8, v);
-        }
-    };
-    auto sstore = [&](int stage, int slot) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < T::PER; ++i) lds[stage][tid + 256 * i] = ring[slot][i];
-    };
-
-    floatx4 acc[WN][4];
-#pragma unroll
-    for (int j = 0; j < WN; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    auto compute = [&](int stage) __attribute__((always_inline)) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            bf16x8 af[WN], bfr[4];
-#pragma unroll
-            for (int j = 0; j < WN; ++j) af[j] = lds[stage][(wn * WN + j) * 128 + h * 64 + lane];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) bfr[i] = lds[stage][T::CHW + (wm * 4 + i) * 128 + h * 64 + lane];
-#pragma unroll
-            for (int j = 0; j < WN; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[j][i] = mfma16x16x32(af[j], bfr[i], acc[j][i]);
-        }
-    };
-
-    // Unit k lives in ring slot k % 2 and LDS stage k % 2.  The loop body is
-    // two straight-line steps with no data-dependent branch, so each LDS store
-    // waits only for its own slot's loads while the other slot's are in
-    // flight; prefetches past the last unit re-read the last unit and their
-    // stages are never computed.
-    const int last = u_begin + (nu > 0 ? nu - 1 : 0);
-    gload(0, u_begin);
-    gload(1, min(u_begin + 1, last));
-    sstore(0, 0);
-    gload(0, min(u_begin + 2, last));
-    for (int k = 0; k < nu; k += 2) {
-        __syncthreads();   // stage 0 holds unit k; stage 1 is no longer read
-        sstore(1, 1);      // unit k + 1
-        gload(1, min(u_begin + k + 3, last));
-        compute(0);
-        if (k + 1 >= nu) break;
-        __syncthreads();   // stage 1 holds unit k + 1; stage 0 is no longer read
-        sstore(0, 0);      // unit k + 2
-        gload(0, min(u_begin + k + 4, last));
-        compute(1);
-    }
-
-    EpiArgs ee = e;
-    if (e.kind == EPI_PARTIAL) ee.y = e.y + (size_t)split * M * e.ldy;
-    const int nb0 = tn * (T::BN / 16) + wn * WN, m0 = tm * PBM + wm * 64;
-    with_kind(e.kind, [&](auto kind) {
-        constexpr int EK = decltype(kind)::value;
-#pragma unroll
-        for (int jh = 0; jh < WN / 2; ++jh) {   // pairs of column blocks: bounds the prefetch registers
-            float4 pre[2][4];
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int n = 16 * (nb0 + 2 * jh + j) + 4 * g, m = m0 + 16 * i + lr;
-                    pre[j][i] = (m < Mv && n < N) ? epi_fetch<EK>(ee, m, n) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int n = 16 * (nb0 + 2 * jh + j) + 4 * g, m = m0 + 16 * i + lr;
-                    if (m < Mv && n < N) epi_store<bf16_t, EK>(ee, m, n, acc[2 * jh + j][i], pre[j][i]);
-                }
-        }
-    });
-}
-
-// ---------------------------------------------------------------- large tiles
-// M >= 256 (prefill, large batches) with fragment-major X.  A workgroup of
+// ---------------------------------------------------------------- tiles
+// M > 64 with fragment-major X.  A workgroup of
 // 4 WM waves (WM x 4) owns a (16 TI WM)-token x (64 TJ)-column output tile; wave
 // (wm, wn) computes 16 TI tokens x 16 TJ columns.
 // What bounds such a tile is the traffic behind the MFMAs.  With both operands
@@ -930,62 +775,59 @@ StreamCfg stream_cfg(int N, int K, bool partial) {
     return StreamCfg{nw, ks, depth, 1};
 }
 
-// K split of the pipelined kernel (O and down projections, whose residual
-// epilogue can take fp32 partials): measured on MI355X at 512-736 tokens, 4
-// ways while the tiles alone give fewer than 256 workgroups, 2 below 512; at
-// least 8 k units per split.
-int pipe_split(int M, int N, int K) {
-    const int tiles = ((M + PBM - 1) / PBM) * ((N + PipeTile<4>::BN - 1) / PipeTile<4>::BN);
-    int S = tiles < 256 ? 4 : (tiles < 512 ? 2 : 1);
-    while (S > 1 && K / 64 / S < 8) S /= 2;
-    return S;
-}
-
-// Large-tile kernel choice for M >= 256: tiles of 128 x 192, 192 x 128, 128 x 128
-// or 256 x 192 (rows x columns).  A CU's tiles run side by side, so a launch
-// takes about as long as the CU with the most tiles: ceil(tiles / 256) times a
-// tile's time, its work over the tile's rate plus a fixed part (prologue and
-// epilogue; longest for 256 x 192, whose one workgroup fills the CU).  Rates and
-// fixed parts are fitted to sweeps on MI355X over 320 to 8192 rows and the
-// projections of the 8B and 7B shapes with weights cold in cache (22 shapes; the
-// model's pick is within 1 % of the best of the four on average, at worst 12 %).
-// No tile is best everywhere: 1024 x 4608 x 3584 takes 40 us with 192 x 128 (56
-// with 128 x 128), 640 x 12288 x 4096 72 us with 128 x 128 (89 with 128 x 192),
-// 1024 x 37888 x 3584 231 us with 128 x 192 (260 with 128 x 128), and 1024 x 3584 x
-// 18944 in three splits 114 us with 256 x 192 (127 with 192 x 128).
-// Split-K (residual) epilogues split K up to 4 ways, at least 8 k units each; a
-// split adds its partial's pass through the residual-norm kernel, about 4.4
-// bytes per nanosecond.  They take 128 x 192 only from 4096 rows, where one split
-// fills the chip (8192 x 3584 x 18944: 914 us, 1034 with 256 x 192); below that
-// 256 x 192 or 192 x 128 splits are faster.  Other epilogues leave 256 x 192 out:
-// inside a step 128 x 192 was faster there (1024 x 37888 x 3584: 235 against 275
-// us), most of all for LM-head launches, whose row count the host does not know
-// (320 of at most 1024 rows: 414 against 554 us).
+// Tile of the M > 64 kernel, by the time model below: a CU's tiles run side by
+// side, so a launch computes for about as long as the CU with the most tiles,
+// ceil(tiles / 256) times a tile's time (its work over the tile's rate plus a
+// fixed part for prologue and epilogue), and reads the weights from HBM for
+// 2 N K bytes / 5 TB/s + 4 us; the shorter of the two hides but for a third.
+// Rates and fixed parts are fitted to a sweep on MI355X of 72 to 2048 rows over
+// the projections of the 8B and 7B shapes, weights cold in cache (140 shapes; the
+// pick is within 2 % of the best tile on average).  No tile is best everywhere:
+// 192 x 24576 x 4096 takes 55 us with 192 x 128 (71 with 128 x 128), 128 x 12288 x
+// 4096 35 us with 96 x 128 (44 with 128 x 128), 96 x 4608 x 3584 18 us with 64 x 64
+// (32 with 128 x 128), 1024 x 37888 x 3584 231 us with 128 x 192 (260 with 128 x
+// 128), 1024 x 3584 x 18944 in three splits 114 us with 256 x 192 (127 with 192 x
+// 128).  (Below 256 rows one 128 x 128 tile through a register ring and an LDS double
+// buffer, two k units ahead, took 79, 50, 42 us for the first three.)
+// Split-K (residual) epilogues split K up to 4 ways, up to 8 below 256 rows, at
+// least 4 k units each; a split adds its partial's pass through the
+// residual-norm kernel, about 4.4 bytes per nanosecond.  They take 128 x 192 only
+// from 4096 rows, where one split fills the chip (8192 x 3584 x 18944: 914 us,
+// 1034 with 256 x 192).  Other epilogues leave 256 x 192 out: inside a step
+// 128 x 192 was faster there (1024 x 37888 x 3584: 235 against 275 us), most of all
+// for LM-head launches, whose row count the host does not know (320 of at most
+// 1024 rows: 414 against 554 us); with fused partials those take tiles of 128
+// columns or more, the merge's limit.
 struct BigCfg {
-    int ti, tj, split;   // tile in units of 32 rows / columns; ti == 0: not a large-tile launch
+    int ti, tj, split;   // tile in units of 32 rows / columns
 };
-BigCfg big_cfg(int M, int N, int K, bool partial) {
-    if (M < 256) return BigCfg{0, 0, 1};
+BigCfg big_cfg(int M, int N, int K, bool partial, bool fused_head = false) {
     struct Tile {
         int ti, tj;
         double rate, fixed_us;   // multiply-adds per microsecond and CU in millions; per tile
     };
-    const Tile cand[4] = {{4, 6, 2.8, 4.0}, {6, 4, 2.75, 5.0}, {4, 4, 2.2, 3.0}, {8, 6, 2.85, 10.0}};
+    const Tile cand[7] = {{4, 6, 2.8, 5.0}, {6, 4, 2.8, 6.0}, {4, 4, 2.4, 4.0}, {3, 4, 2.0, 4.5},
+                          {4, 2, 1.6, 2.0}, {2, 2, 1.2, 1.0}, {8, 6, 2.85, 10.0}};
     BigCfg best{0, 0, 1};
     double best_t = 0.0;
     for (const Tile& c : cand) {
-        if (partial ? c.ti == 4 && c.tj == 6 && M < 4096 : c.ti == 8) continue;
+        const bool t128x192 = c.ti == 4 && c.tj == 6;
+        if (partial ? t128x192 && M < 4096 : c.ti == 8) continue;
+        if (fused_head && c.tj < 4) continue;
         // a tile's 32-bit byte offsets: rows (columns) x K x 2 stay under 4 GiB
-        if (!(c.ti == 4 && c.tj == 4) && K > (1 << 22)) continue;
+        if ((c.ti > 4 || c.tj > 4) && K > (1 << 22)) continue;
         const int bm = 32 * c.ti, bn = 32 * c.tj;
         const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-        for (int S = 1; S <= (partial ? 4 : 1); ++S) {
-            if (S > 1 && K / 64 / S < 8) break;
+        for (int S = 1; S <= (partial ? (M < 256 ? 8 : 4) : 1); ++S) {
+            if (S > 1 && K / 64 / S < (M < 256 ? 4 : 8)) break;
+            if (S == 5 || S == 7) continue;
             const long per_cu = (tiles * S + 255) / 256;
             // three 128 x 192 tiles share a CU: they reach their rate when more follow
-            const double rate = c.ti == 4 && c.tj == 6 && per_cu <= 3 ? 2.6 : c.rate;
-            const double tile_us = (double)bm * bn * K / S / (1e6 * rate) + c.fixed_us;
-            const double us = per_cu * tile_us + (S > 1 ? 4.0 * S * M * N / 4.4e6 : 0.0);
+            const double rate = t128x192 && per_cu <= 3 ? 2.65 : c.rate;
+            const double calc = per_cu * ((double)bm * bn * K / S / (1e6 * rate) + c.fixed_us);
+            const double mem = 2.0 * N * K / 5e6 + 4.0;
+            const double us = (calc > mem ? calc + 0.35 * mem : mem + 0.35 * calc) +
+                              (S > 1 ? 4.0 * S * M * N / 4.4e6 : 0.0);
             if (best.ti == 0 || us < best_t) {
                 best = BigCfg{c.ti, c.tj, S};
                 best_t = us;
@@ -995,7 +837,7 @@ BigCfg big_cfg(int M, int N, int K, bool partial) {
     return best;
 }
 
-void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t* plan) {
+void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t* plan, bool fused_head) {
     plan[1] = plan[2] = 0;
     plan[3] = 1;
     if (dtype == DARD_DTYPE_F32) {
@@ -1016,26 +858,16 @@ void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t
         plan[2] = TBN / 32;
         return;
     }
-    const BigCfg c = big_cfg(M, N, K, partial);
-    if (c.ti) {
-        plan[0] = DARD_GEMM_BIG;
-        plan[1] = c.ti;
-        plan[2] = c.tj;
-        plan[3] = c.split;
-        return;
-    }
-    plan[0] = DARD_GEMM_PIPE;
-    plan[1] = PBM / 32;
-    plan[2] = PipeTile<4>::BN / 32;
-    plan[3] = partial ? pipe_split(M, N, K) : 1;
+    const BigCfg c = big_cfg(M, N, K, partial, fused_head);
+    plan[0] = M < 256 ? DARD_GEMM_PIPE : DARD_GEMM_BIG;
+    plan[1] = c.ti;
+    plan[2] = c.tj;
+    plan[3] = c.split;
 }
 
 int gemm_split(int dtype, int M, int N, int K) {
     if (dtype != DARD_DTYPE_BF16) return 1;
-    if (M > 64) {
-        const BigCfg c = big_cfg(M, N, K, true);
-        return c.ti ? c.split : pipe_split(M, N, K);
-    }
+    if (M > 64) return big_cfg(M, N, K, true).split;
     return stream_cfg(N, K, true).split;
 }
 
@@ -1076,26 +908,21 @@ hipError_t launch_gemm(int dtype, const void* X, int M, int K, int ldx, const vo
         return hipGetLastError();
     }
     if (xfrag) {
-        const BigCfg c = big_cfg(M, N, K, e.kind == EPI_PARTIAL);
-        if (c.ti && e.kind == EPI_LMHEAD && e.lpart && e.ntile != (N + 32 * c.tj - 1) / (32 * c.tj))
-            return hipErrorInvalidValue;
-        if (c.ti) {
-            const int tiles_m = (M + 32 * c.ti - 1) / (32 * c.ti), tiles_n = (N + 32 * c.tj - 1) / (32 * c.tj);
-            const dim3 grid(tiles_m * tiles_n, c.split);
-            if (c.ti == 8)
-                launch(gemm_big_bf16<8, 3, 2, 4, 3, 2>, grid, dim3(512), 0, s, x, M, K, w, N, e, tiles_n);
-            else if (c.ti == 6)
-                launch(gemm_big_bf16<12, 2, 1, 3, 3, 2>, grid, dim3(256), 0, s, x, M, K, w, N, e, tiles_n);
-            else if (c.tj == 6)
-                launch(gemm_big_bf16<8, 3, 1, 3, 2, 3>, grid, dim3(256), 0, s, x, M, K, w, N, e, tiles_n);
-            else
-                launch(gemm_big_bf16<8, 2, 1, 3, 4, 3>, grid, dim3(256), 0, s, x, M, K, w, N, e, tiles_n);
-            return hipGetLastError();
-        }
-        if (e.kind == EPI_LMHEAD && e.lpart) return hipErrorInvalidValue;   // partials need the large tiles
-        const int tiles_m = (M + PBM - 1) / PBM, tiles_n = (N + PipeTile<4>::BN - 1) / PipeTile<4>::BN;
-        const int S = e.kind == EPI_PARTIAL ? pipe_split(M, N, K) : 1;
-        launch(gemm_pipe_bf16<4>, dim3(tiles_m * tiles_n, S), dim3(256), 0, s, x, M, K, w, N, e, tiles_m, tiles_n);
+        const bool parts = e.kind == EPI_LMHEAD && e.lpart;
+        const BigCfg c = big_cfg(M, N, K, e.kind == EPI_PARTIAL, parts);
+        const int tiles_m = (M + 32 * c.ti - 1) / (32 * c.ti), tiles_n = (N + 32 * c.tj - 1) / (32 * c.tj);
+        if (parts && e.ntile != tiles_n) return hipErrorInvalidValue;
+        const dim3 grid(tiles_m * tiles_n, c.split);
+#define DARD_GB(TI, TJ, WM, NST, WD, OCC)                                                                       \
+    launch((gemm_big_bf16<TI, TJ, WM, NST, WD, OCC>), grid, dim3(256 * WM), 0, s, x, M, K, w, N, e, tiles_n)
+        if (c.ti == 8) DARD_GB(8, 3, 2, 4, 3, 2);
+        else if (c.ti == 6) DARD_GB(12, 2, 1, 3, 3, 2);
+        else if (c.ti == 3) DARD_GB(6, 2, 1, 4, 4, 3);
+        else if (c.ti == 2) DARD_GB(4, 1, 1, 4, 4, 4);
+        else if (c.tj == 6) DARD_GB(8, 3, 1, 3, 2, 3);
+        else if (c.tj == 4) DARD_GB(8, 2, 1, 3, 4, 3);
+        else DARD_GB(8, 1, 1, 3, 4, 3);
+#undef DARD_GB
         return hipGetLastError();
     }
     const int tiles_m = (M + TBM - 1) / TBM, tiles_n = (N + TBN - 1) / TBN;

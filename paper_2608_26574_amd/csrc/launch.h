@@ -13,7 +13,7 @@ namespace dard {
 
 // bf16 activations that feed a projection GEMM are stored fragment-major, in
 // the layout of the packed weights: the 16 x 64 block (m/16, k/64) is
-// contiguous, so every wave load (streaming GEMM) or tile copy (pipelined
+// contiguous, so every wave load (streaming GEMM) or tile copy (tiled
 // GEMM) of them reads whole 1 KB runs.  Producers (norms, SwiGLU epilogue,
 // attention output) write that layout when frag_rows(dtype, rows) holds;
 // buffers then hold whole blocks (rows rounded up to 64).
@@ -105,8 +105,9 @@ struct EpiArgs {
 hipError_t launch_gemm(int dtype, const void* X, int M, int K, int ldx, const void* W, int N,
                        const EpiArgs& e, int kernel_class, hipStream_t s, bool xfrag = false);
 int gemm_split(int dtype, int M, int N, int K);
-// The kernel and tiling launch_gemm picks for these sizes (dard_gemm_plan).
-void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t* plan);
+// The kernel and tiling launch_gemm picks for these sizes (dard_gemm_plan);
+// fused_head: the LM-head epilogue with column-tile partials.
+void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t* plan, bool fused_head = false);
 // bf16 fragment-major packing (mode 0 plain, 1 rotary-pair rows, 2 gate/up interleave)
 hipError_t launch_pack_frag(const void* src0, const void* src1, void* dst, int N, int K, int mode, int dh,
                             hipStream_t s);

@@ -50,12 +50,19 @@ def reference_kv(w, dims, ids):
 
 
 @pytest.mark.parametrize("b,P,d,F,gu,down", [
-    (1, 257, 512, 1088, (2, 4, 4, 1), (2, 4, 4, 2)),   # 128 x 128, K split in two
-    (1, 385, 512, 4160, (2, 4, 6, 1), (2, 4, 4, 4)),   # 128 x 192
-    (3, 171, 512, 5120, (2, 6, 4, 1), (2, 4, 4, 4)),   # 192 x 128 over sequence boundaries
-    (1, 641, 2048, 4160, (2, 4, 4, 1), (2, 6, 4, 4)),   # 192 x 128, K split in four
-    (1, 1000, 3584, 18944, (2, 4, 6, 1), (2, 8, 6, 3)),   # 256 x 192, K split in three
-    (2, 2050, 1024, 4160, (2, 4, 6, 1), (2, 6, 4, 1)),   # 4096 rows and more
+    (1, 65, 512, 1088, (1, 2, 2, 1), (1, 2, 2, 4)),   # 64 x 64; 64 x 64, 4 splits
+    (1, 97, 2048, 8256, (1, 4, 4, 1), (1, 2, 2, 4)),   # 128 x 128; 64 x 64, 4 splits
+    (3, 41, 1024, 12288, (1, 4, 4, 1), (1, 2, 2, 8)),   # 128 x 128; 64 x 64, 8 splits
+    (1, 150, 4096, 4096, (1, 4, 2, 1), (1, 3, 4, 4)),   # 128 x 64; 96 x 128, 4 splits
+    (1, 160, 4096, 12288, (1, 6, 4, 1), (1, 3, 4, 4)),   # 192 x 128; 96 x 128, 4 splits
+    (3, 83, 1024, 9472, (1, 4, 6, 1), (1, 4, 2, 8)),   # 128 x 192; 128 x 64, 8 splits
+    (1, 255, 3584, 18944, (1, 4, 6, 1), (1, 4, 4, 4)),   # 128 x 192; 128 x 128, 4 splits
+    (1, 257, 512, 1088, (2, 2, 2, 1), (2, 2, 2, 2)),   # 64 x 64; 64 x 64, 2 splits
+    (1, 385, 512, 4160, (2, 4, 6, 1), (2, 2, 2, 4)),   # 128 x 192; 64 x 64, 4 splits
+    (3, 171, 512, 5120, (2, 6, 4, 1), (2, 2, 2, 3)),   # 192 x 128; 64 x 64, 3 splits
+    (1, 641, 2048, 4160, (2, 3, 4, 1), (2, 3, 4, 2)),   # 96 x 128; 96 x 128, 2 splits
+    (1, 1000, 3584, 18944, (2, 4, 6, 1), (2, 8, 6, 3)),   # 128 x 192; 256 x 192, 3 splits
+    (2, 2050, 1024, 4160, (2, 4, 6, 1), (2, 6, 4, 1)),   # 128 x 192; 192 x 128, one split
 ])
 def test_prefill_tilings(b, P, d, F, gu, down):
     print("[case] prefill tilings", b, P, d, F, gu, down, file=sys.stderr, flush=True)
