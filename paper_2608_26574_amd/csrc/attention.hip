@@ -35,7 +35,7 @@
 // Long key ranges may also be split across workgroups (fp32 partials of
 // (o, m, l), merged in split order by a small combine kernel).
 //
-// fp32 path: one thread per (row, head), plain online softmax.
+// fp32 path: a kernel of its own on the fp32 matrix instructions (below).
 #include <type_traits>
 
 #include "common.h"
@@ -657,55 +657,169 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
     *reinterpret_cast<uint2*>(out + o) = make_uint2(w0, w1);
 }
 
-// fp32 path: one thread per (sequence, row, head).
+// fp32 path, on v_mfma_f32_16x16x4_f32.  A workgroup of kWavesF waves serves 16
+// query rows of one head; the waves take interleaved 32-key tiles and are merged
+// through LDS in wave order.  S^T = K Q^T leaves a lane with keys 4g..4g+3 of its
+// token (lane l: token l % 16, g = l / 16), and the B operand of step e of O^T +=
+// V^T P^T is key 4g + e, so the probabilities are used where they are; K, Q and
+// V^T operands are float4 loads whose element e serves MFMA e.  One thread per
+// (row, head) walking every key took 876 us at 64 rows x 4 heads, 128 keys: a
+// serial chain in 4 workgroups; this takes 11 us.
+constexpr int kWavesF = 4, kKeysF = 32;
+
 template <int DH>
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a) {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t total = (size_t)a.b * a.R * a.Hq;
-    if (t >= total) return;
-    const int h = t % a.Hq;
-    const int r = (t / a.Hq) % a.R;
-    const int s = t / ((size_t)a.Hq * a.R);
-    const int kvh = h / (a.Hq / a.Hkv);
+__global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
+    constexpr int NC = DH / 16;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lr = lane & 15, g = lane >> 4;
+    const int tiles = (a.R + 15) / 16;             // grid: row tile fastest, then head, then sequence
+    const int h = (int)(blockIdx.x / tiles) % a.Hq, s = blockIdx.x / tiles / a.Hq, kvh = h / (a.Hq / a.Hkv);
+    const int r = (int)(blockIdx.x % tiles) * 16 + lr;
+    const bool row_ok = r < a.R;
+    const int rc = min(r, a.R - 1);
+    const size_t t = ((size_t)s * a.R + rc) * a.Hq + h;
     const float* q = reinterpret_cast<const float*>(a.q) + t * DH;
     const float* kb = reinterpret_cast<const float*>(a.k) + ((size_t)s * a.Hkv + kvh) * a.cap * DH;
     const float* vb = reinterpret_cast<const float*>(a.v) + ((size_t)s * a.Hkv + kvh) * a.cap * DH;
     const float* kb_sh = a.P_sh ? reinterpret_cast<const float*>(a.k_sh) + (size_t)kvh * a.cap_sh * DH : kb;
     const float* vb_sh = a.P_sh ? reinterpret_cast<const float*>(a.v_sh) + (size_t)kvh * a.cap_sh * DH : vb;
-    float qr[DH], o[DH];
-    for (int e = 0; e < DH; ++e) { qr[e] = q[e]; o[e] = 0.f; }
-    float m = -INFINITY, l = 0.f;
+    floatx4 qf[NC], o[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        qf[c] = ld_f4(q + 16 * c + 4 * g);
+        o[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
     // rows before ctx_rows lie outside the block: x keys only
-    const bool ctx = a.masked && r < a.ctx_rows;
-    const int rb = r - a.ctx_rows;
+    const bool ctx = a.masked && rc < a.ctx_rows;
+    const int rb = rc - a.ctx_rows;
     const int i = a.masked && !ctx ? rb % a.B : 0;
     const bool shadow = a.masked && !ctx && rb >= a.B;
     const uint8_t* st = a.masked ? a.state + (size_t)s * a.B : nullptr;
     const float* cf = a.masked ? a.conf + (size_t)s * a.B : nullptr;
-    for (int key = 0; key < a.nkeys; ++key) {
-        if (a.masked && key >= a.P) {
-            const int j = key - a.P;
-            const int jj = j < a.B ? j : j - a.B;
-            const bool bx = ctx || take_x(st[i], st[jj], cf[i], cf[jj], i, jj, shadow, a.flags);
-            if (bx != (j < a.B)) continue;
-        }
-        const bool sh = key < a.P_sh;
+    const int si = a.masked ? st[i] : 0;
+    const float ci = a.masked ? cf[i] : 0.f;
+    float m = -INFINITY, l = 0.f;
+    for (int k0 = wave * kKeysF; k0 < a.nkeys; k0 += kWavesF * kKeysF) {
+        const bool sh = k0 < a.P_sh;               // (P_sh % 64 == 0: whole tiles)
         const float* kk = sh ? kb_sh : kb;
         const float* vv = sh ? vb_sh : vb;
         const int vcap = sh ? a.cap_sh : a.cap;
-        float sdot = 0.f;
-        for (int e = 0; e < DH; ++e) sdot += qr[e] * kk[(size_t)key * DH + e];
-        sdot *= a.scale;
-        const float mn = fmaxf(m, sdot);
-        const float alpha = expf(m - mn);
-        const float p = expf(sdot - mn);
-        l = l * alpha + p;
-        for (int e = 0; e < DH; ++e) o[e] = o[e] * alpha + p * vv[(size_t)e * vcap + key];
-        m = mn;
+        floatx4 sc[2], vf[2][NC];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const float* kr = kk + (size_t)min(k0 + 16 * b + lr, a.nkeys - 1) * DH + 4 * g;
+            floatx4 kf[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) kf[c] = ld_f4(kr + 16 * c);
+            // V^T rows: keys past the last one read as zero
+            const int kv = k0 + 16 * b + 4 * g;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const float* vr = vv + (size_t)(16 * c + lr) * vcap + kv;
+                if (kv + 4 <= a.nkeys) {
+                    vf[b][c] = ld_f4(vr);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) vf[b][c][e] = kv + e < a.nkeys ? vr[e] : 0.f;
+                }
+            }
+            sc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sc[b] = mfma16x16x4f(kf[c][e], qf[c][e], sc[b]);
+        }
+        // scale, mask, online softmax over the tile
+        float mt = m;
+        uint32_t vis = 0;                          // bit 4b + e: the row sees key k0 + 16b + 4g + e
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int key = k0 + 16 * b + 4 * g + e;
+                bool see = key < a.nkeys;
+                if (a.masked && key >= a.P && see) {
+                    const int j = key - a.P, jj = j < a.B ? j : j - a.B;
+                    const bool bx = ctx || take_x(si, st[jj], ci, cf[jj], i, jj, shadow, a.flags);
+                    see = bx == (j < a.B);
+                }
+                sc[b][e] *= a.scale;
+                if (see) { vis |= 1u << (4 * b + e); mt = fmaxf(mt, sc[b][e]); }
+            }
+        mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
+        mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+        const float alpha = m == -INFINITY ? 0.f : expf(m - mt);
+        float ps = 0.f;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float p = (vis >> (4 * b + e)) & 1u ? expf(sc[b][e] - mt) : 0.f;
+                sc[b][e] = p;
+                ps += p;
+            }
+        l = l * alpha + ps;
+        m = mt;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) o[c] *= alpha;
+        // a key that a row does not see adds nothing to it, whatever V holds there:
+        // 0 times an infinity or NaN must not reach the row
+        bool odd = false;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) odd |= !(fabsf(vf[b][c][e]) < INFINITY);
+        if (!__any(odd)) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[c] = mfma16x16x4f(vf[b][c][e], sc[b][e], o[c]);
+        } else {
+            for (int key = 0; key < kKeysF; ++key) {
+                const int b = key >> 4, gk = (key >> 2) & 3, e = key & 3;
+                const float p = __shfl(b ? (e < 2 ? (e ? sc[1][1] : sc[1][0]) : (e == 2 ? sc[1][2] : sc[1][3]))
+                                         : (e < 2 ? (e ? sc[0][1] : sc[0][0]) : (e == 2 ? sc[0][2] : sc[0][3])),
+                                       lr + 16 * gk, 64);
+                const uint32_t v = __shfl((int)vis, lr + 16 * gk, 64);
+                if (!((v >> (4 * b + e)) & 1u)) continue;
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d)
+                        o[c][d] += p * vv[(size_t)(16 * c + 4 * g + d) * vcap + k0 + key];
+            }
+        }
     }
+    // l holds this lane's keys only: sum over the row's four lanes
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    __shared__ floatx4 po[kWavesF][NC][64];
+    __shared__ float pm[kWavesF][16], pl[kWavesF][16];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) po[wave][c][lane] = o[c];
+    if (g == 0) { pm[wave][lr] = m; pl[wave][lr] = l; }
+    __syncthreads();
+    float mm = pm[0][lr];
+#pragma unroll
+    for (int w = 1; w < kWavesF; ++w) mm = fmaxf(mm, pm[w][lr]);
+    float f[kWavesF], lt = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWavesF; ++w) {
+        f[w] = pm[w][lr] == -INFINITY ? 0.f : expf(pm[w][lr] - mm);
+        lt += pl[w][lr] * f[w];
+    }
+    const float inv = lt > 0.f ? 1.f / lt : 0.f;
+    if (!row_ok) return;
     float* out = reinterpret_cast<float*>(a.out) + t * DH;
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-    for (int e = 0; e < DH; ++e) out[e] = o[e] * inv;
+    for (int c = wave; c < NC; c += kWavesF) {
+        floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWavesF; ++w) v += po[w][c][lane] * f[w];
+        st_f4(out + 16 * c + 4 * g, v * inv);
+    }
 }
 
 // Shape of a bf16 launch (kernel-trace sweeps at the workload shapes):
@@ -812,12 +926,11 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
         return hipGetLastError();
     }
     if (a.kv_fp8) return hipErrorInvalidValue;   // the fp8 cache is a bf16-model variant
-    const size_t total = (size_t)a.b * a.R * a.Hq;
-    dim3 grid((total + 63) / 64);
-    if (a.dh == 128)
-        launch(attn_f32_kernel<128>, grid, dim3(64), 0, s, a);
-    else
-        launch(attn_f32_kernel<64>, grid, dim3(64), 0, s, a);
+    const size_t wgs = (size_t)((a.R + 15) / 16) * a.Hq * a.b;
+    if (wgs > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)wgs), block(64 * kWavesF);
+    if (a.dh == 128) launch(attn_f32_kernel<128>, grid, block, 0, s, a);
+    else launch(attn_f32_kernel<64>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -87,6 +87,23 @@ __device__ __forceinline__ floatx16 mfma32x32x16(bf16x8 a, bf16x8 b, floatx16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// D(16x16) += A(16x4) * B(4x16), fp32.  Lane l holds A[l%16][l/16],
+// B[l/16][l%16] and D[4*(l/16) .. +3][l%16].
+__device__ __forceinline__ floatx4 mfma16x16x4f(float a, float b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Four floats from an address that is only 4-byte aligned (the fp32 entry points
+// take any float pointer): one 16-byte load all the same.
+__device__ __forceinline__ floatx4 ld_f4(const float* p) {
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    return *reinterpret_cast<const f4u*>(p);
+}
+__device__ __forceinline__ void st_f4(float* p, floatx4 v) {
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    *reinterpret_cast<f4u*>(p) = v;
+}
+
 // s_waitcnt immediate: at most n vector-memory operations outstanding, no LDS
 // operation outstanding (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt
 // 6:4 left at its maximum, lgkmcnt 11:8 zero).
