@@ -650,7 +650,10 @@ int step_tail(const Fwd& f, const dard_params* params, int b, int B, const void*
               const dard_step_debug* dbg) {
     const dard_dims* d = f.d;
     const int rows = b * 2 * B, V = d->vocab, D = d->d_model, dt = d->dtype;
-    float* logits = (float*)(f.ws + f.W.logits);
+    // captured logits are the step's own logits, formed in the caller's buffer
+    // (a buffer off 16-byte alignment gets a copy)
+    const bool direct = dbg && dbg->logits && (reinterpret_cast<uintptr_t>(dbg->logits) & 15) == 0;
+    float* logits = direct ? dbg->logits : (float*)(f.ws + f.W.logits);
     float* cpv = (float*)(f.ws + f.W.cpart_v);
     float* cpm = (float*)(f.ws + f.W.cpart_m);
     float* wbuf = (float*)(f.ws + f.W.w);
@@ -700,7 +703,7 @@ int step_tail(const Fwd& f, const dard_params* params, int b, int B, const void*
         c.phase = 1; c.w = wbuf; c.part = cpm;
         HIPOK(launch_conf_partial(c, stats, f.s));
         if (int rc = final_phase()) return rc;
-        if (dbg && dbg->logits)
+        if (dbg && dbg->logits && !direct)
             HIPOK(hipMemcpyAsync(dbg->logits, logits, (size_t)rows * V * 4, hipMemcpyDeviceToDevice, f.s));
         return DARD_OK;
     }
@@ -724,7 +727,8 @@ int step_tail(const Fwd& f, const dard_params* params, int b, int B, const void*
         }
         EpiArgs e{};
         e.kind = EPI_LMHEAD; e.y = logits; e.ldy = V; e.rowmap = rm; e.rows_dev = count;
-        e.y2 = dbg ? dbg->logits : nullptr;
+        e.y2 = dbg && !direct ? dbg->logits : nullptr;
+        e.store_all = direct;
         if (fused) { e.lpart = lpart; e.ntile = (V + tile_cols - 1) / tile_cols; }
         HIPOK(launch_gemm(dt, hx, max_rows, D, D, head_w, V, e, DARD_K_GEMM_HEAD, f.s, frag_rows(dt, max_rows)));
         if (fused) {

@@ -4,7 +4,13 @@
 // sequence, one thread per block position.  Distance-weighted sums are formed
 // in float64 in position order from a table of lambda^k.  In step mode the
 // vocab-chunk partials of the confidence reduction are first copied to LDS
-// in one coalesced pass and merged there in chunk order.
+// in one coalesced pass; the 256 / B lanes that a position has share the merge
+// of its partials (runs combined by a butterfly), and the sums of Eq. 5-6 walk
+// only the promoted and demoted positions.  The kernel is one workgroup per
+// sequence and nothing but latency: verification and transitions took 8 and 9 us
+// at B = 32 with one lane per position and every position in the sums, 16 and 14
+// at B = 128, and take 8 and 6, 14 and 11 (reading the partials where they are
+// instead of through LDS: 8 and 7, 17 and 10).
 //
 // Sec. 5.1 variants: with a fixed weight every M position takes w_fixed
 // instead of Eq. 5-6; with the entropy or margin ordering the key carried to
@@ -32,27 +38,42 @@ struct Red {
     float t, m2;   // statistics partials only: sum e (l - max), second-largest l
 };
 
-// Merge the chunk partials of one row (stride K floats each) in chunk order.
-__device__ Red combine(const float* p, int nchunk, int K) {
+__device__ __forceinline__ Red merge_red(const Red& x, const Red& y, bool stats) {
+    Red r;
+    const bool take = (y.m > x.m) || (y.m == x.m && y.a < x.a);
+    r.m = fmaxf(x.m, y.m);
+    r.a = take ? y.a : x.a;
+    const float e1 = x.m == -INFINITY ? 0.f : exp2f((x.m - r.m) * kLog2e);
+    const float e2 = y.m == -INFINITY ? 0.f : exp2f((y.m - r.m) * kLog2e);
+    r.s = x.s * e1 + y.s * e2;
+    r.t = 0.f;
+    r.m2 = -INFINITY;
+    if (stats) {
+        const float t1 = x.m == -INFINITY ? 0.f : e1 * (x.t + (x.m - r.m) * x.s);
+        const float t2 = y.m == -INFINITY ? 0.f : e2 * (y.t + (y.m - r.m) * y.s);
+        r.t = t1 + t2;
+        r.m2 = fmaxf(fminf(x.m, y.m), fmaxf(x.m2, y.m2));
+    }
+    return r;
+}
+
+// Merge the chunk partials of one row (stride K floats each): lane `sub` of the
+// row's `lanes` (a power of two, consecutive lanes of one wave, all of them here)
+// takes chunks sub, sub + lanes, ...; every lane of the row gets the result of the
+// same merges.
+__device__ Red combine(const float* p, int nchunk, int K, int sub, int lanes) {
     const bool stats = K == kConfStatsStride;
-    Red t{p[0], __float_as_int(p[1]), p[2], stats ? p[3] : 0.f, stats ? p[4] : -INFINITY};
-    for (int c = 1; c < nchunk; ++c) {
+    Red t{-INFINITY, 0x7fffffff, 0.f, 0.f, -INFINITY};
+    for (int c = sub; c < nchunk; c += lanes) {
         const float* q = p + (size_t)c * K;
-        const float m2 = q[0], s2 = q[2];
-        const int a2 = __float_as_int(q[1]);
-        const float mm = fmaxf(t.m, m2);
-        const bool take = (m2 > t.m) || (m2 == t.m && a2 < t.a);
-        const float e1 = t.m == -INFINITY ? 0.f : exp2f((t.m - mm) * kLog2e);
-        const float e2 = m2 == -INFINITY ? 0.f : exp2f((m2 - mm) * kLog2e);
-        if (stats) {
-            const float t1 = t.m == -INFINITY ? 0.f : e1 * (t.t + (t.m - mm) * t.s);
-            const float t2 = m2 == -INFINITY ? 0.f : e2 * (q[3] + (m2 - mm) * s2);
-            t.t = t1 + t2;
-            t.m2 = fmaxf(fminf(t.m, m2), fmaxf(t.m2, q[4]));
-        }
-        t.a = take ? a2 : t.a;
-        t.s = t.s * e1 + s2 * e2;
-        t.m = mm;
+        const Red y{q[0], __float_as_int(q[1]), q[2], stats ? q[3] : 0.f, stats ? q[4] : -INFINITY};
+        t = c == sub ? y : merge_red(t, y, stats);
+    }
+    for (int o = 1; o < lanes; o <<= 1) {
+        Red y{__shfl_xor(t.m, o, 64), __shfl_xor(t.a, o, 64), __shfl_xor(t.s, o, 64), 0.f, -INFINITY};
+        if (stats) { y.t = __shfl_xor(t.t, o, 64); y.m2 = __shfl_xor(t.m2, o, 64); }
+        // (lower lane first on both sides, so that both hold the same bits)
+        t = (sub & o) ? merge_red(y, t, stats) : merge_red(t, y, stats);
     }
     return t;
 }
@@ -87,18 +108,20 @@ struct PosConf {
     float entropy, margin, key;   // key: the caller's ordering key (array mode)
 };
 
-// Shadow-row confidence of position i: from staged chunk partials (step mode)
-// or from the per-position arrays.
-__device__ PosConf shadow_conf(const DecideArgs& a, const float* part, int s, int i, int tok) {
+// Shadow-row confidence of position i: from its merged partials (step mode) or
+// from the per-position arrays.
+__device__ PosConf shadow_conf(const DecideArgs& a, const Red* red, int s, int i, int tok) {
     PosConf r{0.f, 0.f, 0, 0.f, 0.f, 0.f};
     const int pos = s * a.B + i;
-    if (part) {
-        const Red t = combine(part + (size_t)i * a.nchunk * a.stride, a.nchunk, a.stride);
+    if (red) {
+        const Red t = *red;
         r.maxprob = 1.f / t.s;
         r.argmax = t.a;
-        tok = min(max(tok, 0), (int)a.ld - 1);   // stay inside the row whatever the id
-        const float lc = a.logits[((size_t)s * 2 * a.B + a.B + i) * a.ld + tok];
-        r.pcur = exp2f((lc - t.m) * kLog2e) / t.s;
+        if ((a.flags & DARD_F_VERIFY_PCUR) || a.dbg_pcur_s) {
+            tok = min(max(tok, 0), (int)a.ld - 1);   // stay inside the row whatever the id
+            const float lc = a.logits[((size_t)s * 2 * a.B + a.B + i) * a.ld + tok];
+            r.pcur = exp2f((lc - t.m) * kLog2e) / t.s;
+        }
         if (a.stride == kConfStatsStride) { r.entropy = red_entropy(t); r.margin = red_margin(t); }
     } else {
         r.maxprob = a.maxprob_s[pos];
@@ -120,7 +143,8 @@ __device__ __forceinline__ float order_key(uint32_t flags, bool from_partials, f
 
 __global__ __launch_bounds__(kThreads) void decide_kernel(DecideArgs a, int in_lds) {
     extern __shared__ float staged[];            // [2][B][nchunk][stride] in step mode (in_lds)
-    __shared__ uint8_t promoted[kThreads], demoted[kThreads];
+    __shared__ uint64_t promoted[kBlockWords], demoted[kBlockWords];
+    __shared__ Red rows[kThreads];               // merged partials by position (step mode)
     __shared__ double lam_pow[kThreads];
     __shared__ int all_u, entered_u, bad_code;
     __shared__ float c_all[kThreads];
@@ -142,19 +166,36 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(DecideArgs a, int in_l
         sm = a.part_m ? staged + per_seq : nullptr;
     }
 
-    if (a.phase == DARD_PHASE_VERIFY) {
-        promoted[i] = 0;
-        demoted[i] = 0;
-        if (live) lam_pow[i] = pow(a.lambda, (double)i);
+    if (a.phase == DARD_PHASE_VERIFY && live) lam_pow[i] = pow(a.lambda, (double)i);
+    __syncthreads();
+    // merged partials of every position that has any: 256 / B lanes each
+    if (sv || sm) {
+        int lanes = 1;
+        while (lanes < 64 && lanes * 2 * a.B <= kThreads) lanes *= 2;
+        const int row = i / lanes, sub = i & (lanes - 1);
+        if (row < a.B) {                           // (uniform over a row's lanes)
+            const int rst = a.state_in[s * a.B + row];
+            const float* part = rst == DARD_STATE_C ? sv : (a.phase != DARD_PHASE_VERIFY ? sm : nullptr);
+            if (part) {
+                const Red t = combine(part + (size_t)row * a.nchunk * a.stride, a.nchunk, a.stride, sub, lanes);
+                if (sub == 0) rows[row] = t;
+            }
+        }
         __syncthreads();
+    }
+
+    if (a.phase == DARD_PHASE_VERIFY) {
+        bool up = false, down = false;
         if (live && st == DARD_STATE_C) {
             const int tok = a.tok_in ? a.tok_in[pos] : 0;
-            const PosConf pc = shadow_conf(a, a.part_v ? sv : nullptr, s, i, tok);
+            const PosConf pc = shadow_conf(a, a.part_v ? &rows[i] : nullptr, s, i, tok);
             const float c = pcur_mode ? pc.pcur : pc.maxprob;
             const int nxt = transition(c, a.tau_c, a.tau_u);
-            promoted[i] = nxt == DARD_STATE_U;
-            demoted[i] = nxt == DARD_STATE_M;
+            up = nxt == DARD_STATE_U;
+            down = nxt == DARD_STATE_M;
         }
+        const uint64_t bu = __ballot(up), bd = __ballot(down);
+        if ((i & 63) == 0) { promoted[i >> 6] = bu; demoted[i >> 6] = bd; }
         __syncthreads();
         if (!live) return;
         float w = 0.f;
@@ -162,10 +203,9 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(DecideArgs a, int in_l
             w = a.w_fixed;
         } else if (st == DARD_STATE_M) {
             double P = 0.0, D = 0.0;
-            for (int j = 0; j < a.B; ++j) {
-                const double k = lam_pow[abs(i - j)];
-                if (promoted[j]) P += k;
-                if (demoted[j]) D += k;
+            for (int q = 0; q < kBlockWords; ++q) {
+                for (uint64_t u = promoted[q]; u; u &= u - 1) P += lam_pow[abs(i - (64 * q + __builtin_ctzll(u)))];
+                for (uint64_t u = demoted[q]; u; u &= u - 1) D += lam_pow[abs(i - (64 * q + __builtin_ctzll(u)))];
             }
             w = (float)((P + a.p0) / (P + D + a.p0));
         }
@@ -187,7 +227,7 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(DecideArgs a, int in_l
         if (st == DARD_STATE_M) {
             float given = 0.f;
             if (from_part) {
-                const Red t = combine(sm + (size_t)i * a.nchunk * a.stride, a.nchunk, a.stride);
+                const Red t = rows[i];
                 mp_mix = 1.f / t.s;
                 am_mix = t.a;
                 if (a.stride == kConfStatsStride) { ent = red_entropy(t); mrg = red_margin(t); }
@@ -200,8 +240,7 @@ __global__ __launch_bounds__(kThreads) void decide_kernel(DecideArgs a, int in_l
             xhat = am_mix;
             key = order_key(a.flags, from_part, c, ent, mrg, given);
         } else {
-            const float* part = from_part ? (st == DARD_STATE_C ? sv : sm) : nullptr;
-            const PosConf pc = shadow_conf(a, part, s, i, tok);
+            const PosConf pc = shadow_conf(a, from_part ? &rows[i] : nullptr, s, i, tok);
             mp_s = pc.maxprob; pc_s = pc.pcur; am_s = pc.argmax;
             ent = pc.entropy; mrg = pc.margin;
             c = pcur_mode ? pc.pcur : pc.maxprob;

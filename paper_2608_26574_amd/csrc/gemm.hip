@@ -135,7 +135,7 @@ __device__ __forceinline__ void epi_store(const EpiArgs& e, int m, int n, floatx
         const int code = e.rowmap[m];
         const size_t o = (size_t)(code & kLmRowMask) * e.ldy + n;
         const float4 val = make_float4(v[0], v[1], v[2], v[3]);
-        if (code & kLmStore) *reinterpret_cast<float4*>(e.y + o) = val;
+        if ((code & kLmStore) || e.store_all) *reinterpret_cast<float4*>(e.y + o) = val;
         if (e.y2) *reinterpret_cast<float4*>(e.y2 + o) = val;
     } else if constexpr (EK == EPI_QKV) {
         const QkvRow row = qkv_row(e, m);

@@ -74,12 +74,14 @@ struct EpiArgs {
     // LMHEAD: the rows are listed rows (rowmap codes); rows at or past the
     // device count *rows_dev are skipped (row tiles entirely past it exit
     // before their K loop).  Stored rows go to y (ldy = V) at their logit
-    // row, every row also to y2 when it is set (debug capture); with lpart
-    // the large-tile kernel writes per-column-tile (max, argmax, sum)
-    // partials [M][ntile][3] of every row instead of needing its logits.
+    // row (with store_all every listed row), every row also to y2 when it is
+    // set (debug capture); with lpart the tiled kernel writes per-column-tile
+    // (max, argmax, sum) partials [M][ntile][3] of every row instead of
+    // needing its logits.
     const int32_t* rowmap;
     const int32_t* rows_dev;
     float* y2;
+    int store_all;
     float* lpart;
     int ntile;
     float* y;  int ldy;             // STORE_F32 / RESID (fp32, RESID adds)
