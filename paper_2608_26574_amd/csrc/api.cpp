@@ -111,6 +111,7 @@ Layout layout_of(const dard_dims* d) {
 struct WsLayout {
     size_t h, xn, q, attn, act, sel, part, part_ml, part_slots, gpart, logits, cpart_v, cpart_m, w, ids, tok;
     size_t hx, rowmap, lmcount, lpart;   // the LM head on listed rows (lmhead.hip)
+    size_t gpart_floats;
     size_t total;
 };
 
@@ -151,6 +152,7 @@ WsLayout ws_layout(const dard_dims* d, int b, int B, int cap) {
     const size_t few = rows < 256 ? rows : 256;
     const size_t prow = rows * 4 > 8 * few ? rows * 4 : 8 * few;
     W.gpart = o; o = align256(o + prow * d->d_model * 4);
+    W.gpart_floats = prow * d->d_model;
     // listed LM-head rows: the compact input (whole 64-row blocks), two row
     // lists, their device counts, and the fused column-tile partials (tiles of
     // 128 columns or more)
@@ -568,6 +570,14 @@ int run_layers(const Fwd& f, int R, int P, int B, int step, const uint8_t* state
         }
         a.flags = flags; a.part = (float*)(f.ws + f.W.part); a.part_ml = (float*)(f.ws + f.W.part_ml);
         a.part_slots = f.W.part_slots;
+        if (!masked) {
+            // a prefix pass (its layout has B = 1, so no room of its own): the
+            // split-K partials' buffer is free until the O projection
+            const size_t slots = f.W.gpart_floats / (dh + 2);
+            a.part = (float*)(f.ws + f.W.gpart);
+            a.part_ml = a.part + slots * dh;
+            a.part_slots = slots;
+        }
         a.out_frag = fr;
         a.kv_fp8 = d->kv_format == DARD_KV_FP8;
         {

@@ -36,6 +36,7 @@
 // (o, m, l), merged in split order by a small combine kernel).
 //
 // fp32 path: a kernel of its own on the fp32 matrix instructions (below).
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -186,6 +187,16 @@ void attn_mfma_kernel(AttnArgs a, int rowtiles, int tps) {
     // held), V^T chunks past n are written as zeros (their probabilities are 0
     // and 0 * stale could be NaN), and a chunk that straddles n goes through
     // registers element by element.
+    // byte offsets of this thread's chunks inside a K tile and inside a V^T
+    // tile of the sequence's own cache (the same for every tile)
+    uint32_t koff[NI], voff[NI];
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int q = (wave * NI + j) * 64 + lane;
+        const int r = q / (DH / 8), d = q / (kKeys / 8);
+        koff[j] = (uint32_t)(r * DH + 8 * ((q % (DH / 8)) ^ kswz<DH>(r))) * sizeof(KVT);
+        voff[j] = (uint32_t)(d * cap + 8 * ((q % (kKeys / 8)) ^ vswz(d))) * sizeof(KVT);
+    }
     // FP8 cache: this thread's chunks of the next K and V tiles, held in
     // registers between their loads (early in a step) and their conversion
     // into LDS (at the end of the step, before its barrier)
@@ -193,6 +204,12 @@ void attn_mfma_kernel(AttnArgs a, int rowtiles, int tps) {
     auto load_k8 = [&](int tile) __attribute__((always_inline)) {
         const int k0 = tile_first(tile, npre, P), n = tile_count(tile, npre, pre_end, B2);
         const KVT* kb = k0 < a.P_sh ? kbase_sh : kbase;
+        if (n == kKeys) {   // a full tile: straight-line loads, no per-chunk test
+            const char* kt = reinterpret_cast<const char*>(kb + (size_t)k0 * DH);
+#pragma unroll
+            for (int j = 0; j < NI; ++j) kreg[j] = *reinterpret_cast<const uint2*>(kt + koff[j]);
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int q = (wave * NI + j) * 64 + lane;
@@ -204,10 +221,16 @@ void attn_mfma_kernel(AttnArgs a, int rowtiles, int tps) {
     };
     auto commit_k8 = [&](int tile, char* dst) __attribute__((always_inline)) {
         const int n = tile_count(tile, npre, pre_end, B2);
+        if (n == kKeys) {
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                *reinterpret_cast<uint4*>(dst + 16 * ((wave * NI + j) * 64 + lane)) = e4m3x8_to_bf16x8(kreg[j]);
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int q = (wave * NI + j) * 64 + lane;
-            if (n == kKeys || q / (DH / 8) < n) *reinterpret_cast<uint4*>(dst + 16 * q) = e4m3x8_to_bf16x8(kreg[j]);
+            if (q / (DH / 8) < n) *reinterpret_cast<uint4*>(dst + 16 * q) = e4m3x8_to_bf16x8(kreg[j]);
         }
     };
     auto load_v8 = [&](int tile) __attribute__((always_inline)) {
@@ -215,6 +238,14 @@ void attn_mfma_kernel(AttnArgs a, int rowtiles, int tps) {
         const bool sh = k0 < a.P_sh;
         const KVT* vb = sh ? vbase_sh : vbase;
         const int vcap = sh ? a.cap_sh : cap;
+        // a full tile of the own cache whose chunks are all 8-byte aligned (cap a
+        // multiple of 8, and the tile's first key): straight-line loads
+        if (n == kKeys && !sh && ((cap | (int)(reinterpret_cast<uintptr_t>(vbase + k0))) & 7) == 0) {
+            const char* vt = reinterpret_cast<const char*>(vbase + k0);
+#pragma unroll
+            for (int j = 0; j < NI; ++j) vreg[j] = *reinterpret_cast<const uint2*>(vt + voff[j]);
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int q = (wave * NI + j) * 64 + lane;
@@ -242,16 +273,6 @@ void attn_mfma_kernel(AttnArgs a, int rowtiles, int tps) {
             *reinterpret_cast<uint4*>(dst + 16 * q) = e4m3x8_to_bf16x8(vreg[j]);
         }
     };
-    // byte offsets of this thread's chunks inside a K tile and inside a V^T
-    // tile of the sequence's own cache (the same for every tile)
-    uint32_t koff[NI], voff[NI];
-#pragma unroll
-    for (int j = 0; j < NI; ++j) {
-        const int q = (wave * NI + j) * 64 + lane;
-        const int r = q / (DH / 8), d = q / (kKeys / 8);
-        koff[j] = (uint32_t)(r * DH + 8 * ((q % (DH / 8)) ^ kswz<DH>(r))) * sizeof(KVT);
-        voff[j] = (uint32_t)(d * cap + 8 * ((q % (kKeys / 8)) ^ vswz(d))) * sizeof(KVT);
-    }
     auto issue_k = [&](int tile, char* dst) __attribute__((always_inline)) {
         if constexpr (KV8) {
             load_k8(tile);
@@ -493,6 +514,7 @@ void attn_mfma_kernel(AttnArgs a, int rowtiles, int tps) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (!late) {
+        if constexpr (G > 1) wg_barrier();           // (pairs with the second group's)
         for (int it = 0; it < iters; ++it) {         // iters is uniform across the workgroup
             const bool nextv = mine(it + 1), ahead = mine(it + 2);
             if constexpr (KV8) {
@@ -520,6 +542,9 @@ void attn_mfma_kernel(AttnArgs a, int rowtiles, int tps) {
     } else {
         floatx16 sc[2];
         if (mine(0)) scores(kst(0), sc);
+        // K tile 3 goes over the stage that these scores read: every wave first
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(63));
+        wg_barrier();
         for (int it = 0; it < iters; ++it) {
             const bool nextv = mine(it + 1), ahead = mine(it + 3);
             if constexpr (KV8) {
@@ -825,7 +850,10 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
 // Shape of a bf16 launch (kernel-trace sweeps at the workload shapes):
 // - more than 64 rows per KV head (grouped-query attention, prefill): 4 waves
 //   per group, and a second, phase-shifted key group while the workgroups
-//   alone leave SIMDs idle (7B GQA shape, batch 8: 35.6 -> 31.4 us);
+//   alone leave SIMDs idle (7B GQA shape, batch 8: 35.6 -> 31.4 us); while they
+//   cover less than half of the CUs the keys are split, four tiles or more each
+//   (28 heads over 4 KV heads, mask included: one sequence of 1472 + 64 keys 45 ->
+//   23 us, four of 1024 + 64 40 -> 29 us);
 // - 64 rows (one MHA head's augmented block): with at least 256 workgroups,
 //   2 waves per workgroup (batch 16: 36 us); with few heads (batch 1-2), 4
 //   waves and key splits of about 3 tiles merged by the combine kernel
@@ -835,7 +863,7 @@ struct AttnCfg {
     int waves, g, rowtiles, ns, tps;
 };
 
-AttnCfg attention_cfg(int b, int R, int Hq, int Hkv, int ntiles) {
+AttnCfg attention_cfg(int b, int R, int Hq, int Hkv, int ntiles, bool split_ok = true) {
     AttnCfg c{};
     const int nrows = (Hq / Hkv) * R;
     c.g = 1;
@@ -845,12 +873,16 @@ AttnCfg attention_cfg(int b, int R, int Hq, int Hkv, int ntiles) {
         c.rowtiles = (nrows + 127) / 128;
         const long wgs = (long)b * Hkv * c.rowtiles;
         if (wgs * 4 < 1024 && ntiles >= 4) c.g = 2;
+        if (split_ok && wgs * 2 <= 256 && ntiles >= 8) {
+            const long ns = std::min<long>(std::min<long>(256 / wgs, ntiles / 4), kMaxSplit);
+            c.ns = (int)ns;
+        }
     } else {
         c.rowtiles = 1;
         c.waves = 2;
         const long wgs = (long)b * Hkv;
         const long by_tiles = (ntiles + 2) / 3;
-        if (wgs < 256 && wgs * by_tiles <= 256) {
+        if (split_ok && wgs < 256 && wgs * by_tiles <= 256) {
             // few heads: key splits of about three tiles merged by the combine
             // kernel, 4 waves per workgroup (the extra two only copy tiles)
             c.waves = 4;
@@ -858,7 +890,7 @@ AttnCfg attention_cfg(int b, int R, int Hq, int Hkv, int ntiles) {
         } else if (wgs < 256) {
             // more heads, still short of the chip: splits toward ~128
             // workgroups, and two key groups of two waves taking alternate tiles
-            long ns = (128 + wgs / 2) / wgs;
+            long ns = split_ok ? (128 + wgs / 2) / wgs : 1;
             ns = ns < 1 ? 1 : (ns > kMaxSplit ? kMaxSplit : ns);
             c.ns = (int)ns;
             if ((ntiles + c.ns - 1) / c.ns >= 2) c.g = 2;
@@ -901,13 +933,11 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
         if (a.dh != 64 && a.dh != 128) return hipErrorInvalidValue;
         const int ntiles = attention_tiles(a.masked, a.P, a.B, a.nkeys);
         AttnCfg c = attention_cfg(a.b, a.R, a.Hq, a.Hkv, ntiles);
-        if (a.kv_fp8 && c.waves == 4) c.g = 1;   // see attention_kernel: one key group with the fp8 cache
         // a split needs room for its partials; without it one workgroup walks every key
         const size_t nrow = (size_t)a.b * a.R * a.Hq;
-        if (c.ns > 1 && (!a.part || !a.part_ml || (size_t)c.ns * nrow > a.part_slots)) {
-            c.ns = 1;
-            c.tps = ntiles > 0 ? ntiles : 1;
-        }
+        if (c.ns > 1 && (!a.part || !a.part_ml || (size_t)c.ns * nrow > a.part_slots))
+            c = attention_cfg(a.b, a.R, a.Hq, a.Hkv, ntiles, false);
+        if (a.kv_fp8 && c.waves == 4) c.g = 1;   // see attention_kernel: one key group with the fp8 cache
         const size_t tiles = (size_t)a.b * a.Hkv * c.rowtiles;
         if (tiles == 0 || tiles > 0x7fffffff) return hipErrorInvalidValue;
         dim3 grid((unsigned)tiles, c.ns);
