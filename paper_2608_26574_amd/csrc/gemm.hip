@@ -825,7 +825,7 @@ StreamCfg stream_cfg(int N, int K, bool partial) {
 // 128).  (Below 256 rows one 128 x 128 tile through a register ring and an LDS double
 // buffer, two k units ahead, took 79, 50, 42 us for the first three.)
 // Split-K (residual) epilogues split K up to 4 ways, up to 8 below 256 rows, at
-// least 4 k units each; a split adds its partial's pass through the
+// least 8 k units each; a split adds its partial's pass through the
 // residual-norm kernel, about 4.4 bytes per nanosecond.  They take 128 x 192 only
 // from 4096 rows, where one split fills the chip (8192 x 3584 x 18944: 914 us,
 // 1034 with 256 x 192).  Other epilogues leave 256 x 192 out: inside a step
@@ -854,7 +854,7 @@ BigCfg big_cfg(int M, int N, int K, bool partial, bool fused_head = false) {
         const int bm = 32 * c.ti, bn = 32 * c.tj;
         const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
         for (int S = 1; S <= (partial ? (M < 256 ? 8 : 4) : 1); ++S) {
-            if (S > 1 && K / 64 / S < (M < 256 ? 4 : 8)) break;
+            if (S > 1 && K / 64 / S < 8) break;
             if (S == 5 || S == 7) continue;
             const long per_cu = (tiles * S + 255) / 256;
             // three 128 x 192 tiles share a CU: they reach their rate when more follow

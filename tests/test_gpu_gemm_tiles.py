@@ -50,7 +50,7 @@ def reference_kv(w, dims, ids):
 
 
 @pytest.mark.parametrize("b,P,d,F,gu,down", [
-    (1, 65, 512, 1088, (1, 2, 2, 1), (1, 2, 2, 4)),   # 64 x 64; 64 x 64, 4 splits
+    (1, 65, 512, 1088, (1, 2, 2, 1), (1, 2, 2, 2)),   # 64 x 64; 64 x 64, 2 splits
     (1, 97, 2048, 8256, (1, 4, 4, 1), (1, 2, 2, 4)),   # 128 x 128; 64 x 64, 4 splits
     (3, 41, 1024, 12288, (1, 4, 4, 1), (1, 2, 2, 8)),   # 128 x 128; 64 x 64, 8 splits
     (1, 150, 4096, 4096, (1, 4, 2, 1), (1, 3, 4, 4)),   # 128 x 64; 96 x 128, 4 splits
