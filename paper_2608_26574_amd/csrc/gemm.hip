@@ -326,6 +326,35 @@ __device__ __forceinline__ void copy16_lds(__amdgpu_buffer_rsrc_t r, char* dst, 
 #endif
 }
 
+// The counted wait in the middle of unit u (see the K loop of gemm_big_bf16): vector
+// memory operations that may stay outstanding there.  Copies between the one waited
+// for and the wait, and in the unrolled loop 2 TJ of the weight loads between them; a
+// tail unit's weight loads are dead code and dropped, so its wait counts none.
+constexpr int mid_wait(bool tail, int TJ, int NST, int CPW) { return (NST - 2) * CPW + (tail ? 0 : 2 * TJ); }
+
+// Whether no wait of a launch of nu units can leave the copy of unit u + 1 in
+// flight: at least mid_wait operations are certain to be issued after that copy.
+// Certain are the copies, the weight loads of the loop's units, and of the prologue's
+// weight loads those whose slots units 0..u have used (the compiler may sink the
+// others).
+constexpr bool waits_cover(int TJ, int NST, int WD, int CPW, int nu) {
+    const int loop_end = nu / WD * WD;
+    for (int u = 0; u + 1 < nu; ++u) {
+        const int c = u + 1 - NST;                 // the unit that copied unit u + 1 (below 0: the prologue)
+        int issued = (NST - 2) * CPW;
+        if (c < 0) issued += 2 * TJ * (u + 1 < WD ? u + 1 : WD);
+        for (int t = c < 0 ? 0 : c; t <= u; ++t)   // half of unit c's follow its copy, half of unit u's come before its wait
+            if (t < loop_end) issued += t == c || t == u ? TJ : 2 * TJ;
+        if (issued < mid_wait(u >= loop_end, TJ, NST, CPW)) return false;
+    }
+    return true;
+}
+constexpr bool waits_cover_all(int TJ, int NST, int WD, int CPW) {
+    for (int nu = 1; nu <= 4 * WD + NST; ++nu)     // the counts repeat from there on
+        if (!waits_cover(TJ, NST, WD, CPW, nu)) return false;
+    return true;
+}
+
 template <int TI, int TJ, int WM, int NST, int WD, int OCC>
 __global__ __launch_bounds__(256 * WM) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 void gemm_big_bf16(const bf16_t* __restrict__ X, int M, int K, const bf16_t* __restrict__ W, int N, EpiArgs e,
@@ -336,6 +365,7 @@ void gemm_big_bf16(const bf16_t* __restrict__ X, int M, int K, const bf16_t* __r
     constexpr int CH = TI / 2;                     // X fragments per chunk
     static_assert(TI % 2 == 0 && NST >= 3, "whole chunks; the wait counts below need three stages");
     static_assert((NST - 1) * CPW + 2 * TJ <= 63, "vmcnt range");
+    static_assert(waits_cover_all(TJ, NST, WD, CPW), "a wait could leave the copy of the next unit in flight");
     static_assert(NST * STAGE >= WM * 4 * TI * 16 * 12, "the epilogue's row partials fit the stages");
     __shared__ __attribute__((aligned(16))) char smem[NST * STAGE];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -428,8 +458,9 @@ void gemm_big_bf16(const bf16_t* __restrict__ X, int M, int K, const bf16_t* __r
     // copied over stage t.  Copies complete in issue order, so stage t + 1 has
     // arrived when at most the (NST - 2) CPW copies issued after it are
     // outstanding, plus the weight loads issued after it: 2 (NST - 1) TJ of
-    // them.  The waits count only 2 TJ (none in the prologue, from where the
-    // compiler may sink weight loads), so moving weight loads cannot break them.
+    // them in the loop.  The waits count only 2 TJ, and none in the prologue, from
+    // where the compiler may sink weight loads, and in the tail units, whose weight
+    // loads nothing uses, so that it drops them (mid_wait, waits_cover).
 #pragma unroll
     for (int p = 0; p < NST; ++p) copy_x(p, p);
     __builtin_amdgcn_sched_barrier(0);
@@ -444,8 +475,9 @@ void gemm_big_bf16(const bf16_t* __restrict__ X, int M, int K, const bf16_t* __r
     __builtin_amdgcn_sched_barrier(0);
     read_x(xa, 0, 0, 0);
     int st0 = 0;
-    auto unit = [&](int u, auto slotc) __attribute__((always_inline)) {
+    auto unit = [&](int u, auto slotc, auto tailc) __attribute__((always_inline)) {
         constexpr int s = decltype(slotc)::value;
+        constexpr bool tail = decltype(tailc)::value != 0;
         const int st1 = st0 + 1 == NST ? 0 : st0 + 1;
         read_x(xb, st0, 0, CH);
         mm(wf[s][0], xa, Kind<0>{});
@@ -458,7 +490,7 @@ void gemm_big_bf16(const bf16_t* __restrict__ X, int M, int K, const bf16_t* __r
         read_x(xb, st0, 1, CH);
         mm(wf[s][1], xa, Kind<0>{});
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm((NST - 2) * CPW + 2 * TJ));   // (and every LDS read)
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(mid_wait(tail, TJ, NST, CPW)));   // (and every LDS read)
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         copy_x(u + NST, st0);
@@ -471,14 +503,14 @@ void gemm_big_bf16(const bf16_t* __restrict__ X, int M, int K, const bf16_t* __r
     };
     int u = 0;
     for (; u + WD <= nu; u += WD) {
-        unit(u, Kind<0>{});
-        if constexpr (WD > 1) unit(u + 1, Kind<1>{});
-        if constexpr (WD > 2) unit(u + 2, Kind<2>{});
-        if constexpr (WD > 3) unit(u + 3, Kind<3>{});
+        unit(u, Kind<0>{}, Kind<0>{});
+        if constexpr (WD > 1) unit(u + 1, Kind<1>{}, Kind<0>{});
+        if constexpr (WD > 2) unit(u + 2, Kind<2>{}, Kind<0>{});
+        if constexpr (WD > 3) unit(u + 3, Kind<3>{}, Kind<0>{});
     }
-    if (u < nu) unit(u, Kind<0>{});
-    if constexpr (WD > 2) if (u + 1 < nu) unit(u + 1, Kind<1>{});
-    if constexpr (WD > 3) if (u + 2 < nu) unit(u + 2, Kind<2>{});
+    if (u < nu) unit(u, Kind<0>{}, Kind<1>{});
+    if constexpr (WD > 2) if (u + 1 < nu) unit(u + 1, Kind<1>{}, Kind<1>{});
+    if constexpr (WD > 3) if (u + 2 < nu) unit(u + 2, Kind<2>{}, Kind<1>{});
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));     // no copy lands after this point
 
     EpiArgs ee = e;
