@@ -457,7 +457,8 @@ dard_status dard_linear(int dtype, const void* X, int M, int K, const void* Wp, 
  *   plan[0] = DARD_GEMM_* kernel, plan[1] x plan[2] = the workgroup tile in
  *   units of 32 rows x 32 columns (the streaming kernel: 16-column blocks
  *   per wave in plan[2]), plan[3] = workgroups splitting K.
- * partial != 0 asks for the plan of a split-K (residual) projection; step
+ * partial != 0 asks for the plan of a residual projection (O or down: K split
+ * plan[3] ways, with 1 the full sum on that tile); step
  * and prefill activations are fragment-major (frag_x != 0), dard_linear's
  * row-major (frag_x = 0).  plan: host int32 [4]. */
 #define DARD_GEMM_STREAM 0

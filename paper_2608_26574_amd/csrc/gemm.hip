@@ -856,19 +856,23 @@ StreamCfg stream_cfg(int N, int K, bool partial) {
 // 128), 1024 x 3584 x 18944 in three splits 114 us with 256 x 192 (127 with 192 x
 // 128).  (Below 256 rows one 128 x 128 tile through a register ring and an LDS double
 // buffer, two k units ahead, took 79, 50, 42 us for the first three.)
-// Split-K (residual) epilogues split K up to 4 ways, up to 8 below 256 rows, at
-// least 8 k units each; a split adds its partial's pass through the
-// residual-norm kernel, about 4.4 bytes per nanosecond.  They take 128 x 192 only
-// from 4096 rows, where one split fills the chip (8192 x 3584 x 18944: 914 us,
-// 1034 with 256 x 192).  Other epilogues leave 256 x 192 out: inside a step
-// 128 x 192 was faster there (1024 x 37888 x 3584: 235 against 275 us), most of all
-// for LM-head launches, whose row count the host does not know (320 of at most
-// 1024 rows: 414 against 554 us); with fused partials those take tiles of 128
-// columns or more, the merge's limit.
+// Residual projections (O and down) may split K up to 4 ways, up to 8 below 256
+// rows, at least 8 k units each; a split adds its partial's pass through the
+// residual-norm kernel, about 4.4 bytes per nanosecond.  One list of tiles serves
+// the decision, the partials and the full sum, so that what is priced is what runs.
+// From 4096 rows, where one split fills the chip, full sums leave 256 x 192 out (8192
+// x 3584 x 18944: 914 us with 128 x 192, 1034 with 256 x 192; a prefill of 8192 rows
+// was 1.6 % slower with it); below, partials leave 128 x 192 out and full sums gain
+// from 256 x 192 (2560 x 4096 x 12288: 221 us, 244 with 192 x 128).  Other epilogues
+// leave 256 x 192 out: inside a step 128 x 192 was faster there (1024 x 37888 x 3584:
+// 235 against 275 us), most of all for LM-head launches, whose row count the host
+// does not know (320 of at most 1024 rows: 414 against 554 us); with fused partials
+// those take tiles of 128 columns or more, the merge's limit.
 struct BigCfg {
     int ti, tj, split;   // tile in units of 32 rows / columns
 };
-BigCfg big_cfg(int M, int N, int K, bool partial, bool fused_head = false) {
+// resid: a residual projection, K split at most max_split ways.
+BigCfg big_cfg(int M, int N, int K, bool resid, int max_split, bool fused_head) {
     struct Tile {
         int ti, tj;
         double rate, fixed_us;   // multiply-adds per microsecond and CU in millions; per tile
@@ -879,15 +883,16 @@ BigCfg big_cfg(int M, int N, int K, bool partial, bool fused_head = false) {
     double best_t = 0.0;
     for (const Tile& c : cand) {
         const bool t128x192 = c.ti == 4 && c.tj == 6;
-        if (partial ? t128x192 && M < 4096 : c.ti == 8) continue;
+        if (!resid && c.ti == 8) continue;
         if (fused_head && c.tj < 4) continue;
         // a tile's 32-bit byte offsets: rows (columns) x K x 2 stay under 4 GiB
         if ((c.ti > 4 || c.tj > 4) && K > (1 << 22)) continue;
         const int bm = 32 * c.ti, bn = 32 * c.tj;
         const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-        for (int S = 1; S <= (partial ? (M < 256 ? 8 : 4) : 1); ++S) {
+        for (int S = 1; S <= max_split; ++S) {
             if (S > 1 && K / 64 / S < 8) break;
             if (S == 5 || S == 7) continue;
+            if (S == 1 ? c.ti == 8 && M >= 4096 : t128x192 && M < 4096) continue;
             const long per_cu = (tiles * S + 255) / 256;
             // three 128 x 192 tiles share a CU: they reach their rate when more follow
             const double rate = t128x192 && per_cu <= 3 ? 2.65 : c.rate;
@@ -910,6 +915,18 @@ BigCfg big_cfg(int M, int N, int K, bool partial, bool fused_head = false) {
 // 128-row tiles and a second pass over the weights: 350 us, 276 us with one of 192.
 int head_rows(int M) { return (3 * M + 3) / 4; }
 
+// The tile of one launch of the M > 64 kernel; the split of a residual projection
+// (EPI_PARTIAL) is the one whose time is least, and where that is 1 the full sum
+// (EPI_RESID) runs on the very tile that was priced.
+BigCfg launch_cfg(int kind, int M, int N, int K, bool fused_head) {
+    switch (kind) {
+    case EPI_PARTIAL: return big_cfg(M, N, K, true, M < 256 ? 8 : 4, false);
+    case EPI_RESID: return big_cfg(M, N, K, true, 1, false);
+    case EPI_LMHEAD: return big_cfg(head_rows(M), N, K, false, 1, fused_head);
+    default: return big_cfg(M, N, K, false, 1, false);
+    }
+}
+
 void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t* plan, bool fused_head) {
     plan[1] = plan[2] = 0;
     plan[3] = 1;
@@ -918,7 +935,8 @@ void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t
         return;
     }
     if (M <= 64) {
-        const StreamCfg c = stream_cfg(N, K, partial);
+        StreamCfg c = stream_cfg(N, K, partial);
+        if (c.split == 1) c = stream_cfg(N, K, false);   // one split runs the full-sum epilogue
         plan[0] = DARD_GEMM_STREAM;
         plan[1] = 4;
         plan[2] = c.nw;
@@ -931,7 +949,7 @@ void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t
         plan[2] = TBN / 32;
         return;
     }
-    const BigCfg c = big_cfg(fused_head ? head_rows(M) : M, N, K, partial, fused_head);
+    const BigCfg c = launch_cfg(fused_head ? EPI_LMHEAD : (partial ? EPI_PARTIAL : EPI_STORE_F32), M, N, K, fused_head);
     plan[0] = M < 256 ? DARD_GEMM_PIPE : DARD_GEMM_BIG;
     plan[1] = c.ti;
     plan[2] = c.tj;
@@ -940,7 +958,7 @@ void gemm_plan(int dtype, int M, int N, int K, bool partial, bool xfrag, int32_t
 
 int gemm_split(int dtype, int M, int N, int K) {
     if (dtype != DARD_DTYPE_BF16) return 1;
-    if (M > 64) return big_cfg(M, N, K, true).split;
+    if (M > 64) return launch_cfg(EPI_PARTIAL, M, N, K, false).split;
     return stream_cfg(N, K, true).split;
 }
 
@@ -988,7 +1006,7 @@ hipError_t launch_gemm(int dtype, const void* X, int M, int K, int ldx, const vo
     }
     if (xfrag) {
         const bool parts = e.kind == EPI_LMHEAD && e.lpart;
-        const BigCfg c = big_cfg(e.kind == EPI_LMHEAD ? head_rows(M) : M, N, K, e.kind == EPI_PARTIAL, parts);
+        const BigCfg c = launch_cfg(e.kind, M, N, K, parts);
         const int tiles_m = (M + 32 * c.ti - 1) / (32 * c.ti), tiles_n = (N + 32 * c.tj - 1) / (32 * c.tj);
         if (parts && e.ntile != tiles_n) return hipErrorInvalidValue;
         const dim3 grid(tiles_m * tiles_n, c.split);

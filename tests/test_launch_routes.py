@@ -1,0 +1,122 @@
+"""What the library launches, on the CPU: a small C library takes the place of
+hipExtLaunchKernel (every kernel start of libdard goes through it) and writes
+down each kernel's name and grid and, for the tiled GEMM, its sizes.  Nothing
+runs and no pointer is followed, so the tile, the K split and the order of a
+forward's launches can be compared with what dard_gemm_plan reports."""
+import json
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+from paper_2608_26574_amd import dard
+
+STAND_IN = r"""
+#include <stdio.h>
+#include <string.h>
+typedef struct { unsigned x, y, z; } dim3;
+static struct { const void* f; const char* name; } known[4096];
+static int n_known;
+void __hipRegisterFunction(void** m, const void* f, char* dev, const char* name, unsigned t, void* a, void* b,
+                           void* c, void* d, int* w) {
+    if (n_known < 4096) { known[n_known].f = f; known[n_known++].name = name; }
+}
+int hipExtLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t lds, void* s, void* e0, void* e1, int fl) {
+    const char* name = "?";
+    for (int i = 0; i < n_known; ++i) if (known[i].f == f) name = known[i].name;
+    int M = 0, K = 0, N = 0, kind = 0;
+    if (strstr(name, "gemm_big_bf16")) { M = *(int*)args[1]; K = *(int*)args[2]; N = *(int*)args[4]; kind = *(int*)args[5]; }
+    if (strstr(name, "gemm_stream_bf16")) { M = *(int*)args[1]; K = *(int*)args[2]; N = *(int*)args[5]; kind = *(int*)args[6]; }
+    printf("[\"%s\", %u, %u, %u, %d, %d, %d, %d]\n", name, g.x, g.y, b.x, kind, M, N, K);
+    return 0;
+}
+int hipGetLastError(void) { return 0; }
+"""
+
+# one prefill of one layer per line of the input: rows, d, ffn
+PROGRAM = r"""
+import ctypes, sys
+ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+L = ctypes.CDLL(sys.argv[2])
+L.dard_workspace_bytes.restype = ctypes.c_size_t
+fake = ctypes.c_void_p(1 << 20)
+for line in sys.stdin:
+    M, d, F = map(int, line.split())
+    dims = (ctypes.c_int32 * 12)(1, d, d // 128, max(1, d // 256), 128, F, 1040, 1 << 20, 1)
+    ctypes.cast(dims, ctypes.POINTER(ctypes.c_float))[10] = 1e4
+    ws = L.dard_workspace_bytes(dims, 1, 1, M + 2)
+    rc = L.dard_prefill(dims, fake, fake, M + 2, 1, M, fake, None, fake, ctypes.c_size_t(ws), None)
+    ctypes.CDLL(None).fflush(None)
+    print("end", rc, flush=True)
+"""
+
+STORE, RESID, SWIGLU, QKV, PARTIAL = range(5)
+
+
+@pytest.fixture(scope="module")
+def prefills(tmp_path_factory):
+    """cases [(M, d, F)] -> per case the launches (kernel, grid x, y, threads, kind, M, N, K)."""
+    folder = tmp_path_factory.mktemp("standin")
+    src, so = folder / "standin.c", folder / "standin.so"
+    src.write_text(STAND_IN)
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-w", "-o", str(so), str(src)], check=True)
+
+    def run(cases):
+        r = subprocess.run([sys.executable, "-c", PROGRAM, str(so), os.path.abspath(dard.LIB_PATH)],
+                           input="".join("%d %d %d\n" % c for c in cases), capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        out, cur = [], []
+        for line in r.stdout.splitlines():
+            if line.startswith("end"):
+                assert line == "end 0", line
+                out.append(cur)
+                cur = []
+            else:
+                cur.append(json.loads(line))
+        assert len(out) == len(cases)
+        return out
+
+    return run
+
+
+def tile(launch):
+    """(rows / 32, columns / 32, K split) of a launch of the tiled GEMM: template
+    arguments TI, TJ, WM give 16 TI WM rows and 64 TJ columns."""
+    ti, tj, wm = map(int, re.search(r"gemm_big_bf16ILi(\d+)ELi(\d+)ELi(\d+)E", launch[0]).groups())
+    return ti * wm // 2, 2 * tj, launch[2]
+
+
+# the projections of 4096 and 3584 wide models over row counts on both sides of
+# every change of tile, K too short for a split, and full sums on 256 x 192 tiles
+# (2560 x 4096 x 12288, 8192 x 4096 x 4096, 700 x 320 x 8192)
+CASES = [(M, d, F) for d, F in ((4096, 12288), (3584, 18944), (1024, 4160))
+         for M in (65, 97, 160, 255, 256, 300, 651, 1000, 2048, 2100, 2560, 2816, 3000, 3500, 4096, 5000, 6000, 8192,
+                   16000)] + [(700, 8192, 320), (700, 512, 128)]
+
+
+def test_tiles_that_run_are_the_tiles_of_the_plan(prefills):
+    full_256 = 0
+    for (M, d, F), launches in zip(CASES, prefills(CASES)):
+        gemms = [x for x in launches if "gemm_big_bf16" in x[0]]
+        assert len(gemms) == 4, (M, d, F, launches)   # QKV, O, gate/up, down
+        for x, (N, K, kinds) in zip(gemms, (((d // 128 + 2 * max(1, d // 256)) * 128, d, (QKV,)), (d, d, (RESID, PARTIAL)),
+                                            (2 * F, d, (SWIGLU,)), (d, F, (RESID, PARTIAL)))):
+            assert x[5:] == [M, N, K] and x[4] in kinds, (M, d, F, x)
+            plan = dard.dard_gemm_plan(M, N, K, partial=x[4] in (RESID, PARTIAL))
+            assert tile(x) == plan[1:], (M, N, K, x[0], plan)
+            assert (x[4] == PARTIAL) == (x[4] in (RESID, PARTIAL) and plan[3] > 1), (M, N, K, x, plan)
+            full_256 += x[4] == RESID and tile(x) == (8, 6, 1)
+    assert full_256 >= 3   # the full sums on 256 x 192 tiles are among the cases
+
+
+def test_streaming_tiles_that_run_are_the_tiles_of_the_plan(prefills):
+    cases = [(M, d, F) for M in (1, 17, 64) for d, F in ((512, 1088), (4096, 12288), (384, 512), (1024, 960))]
+    for (M, d, F), launches in zip(cases, prefills(cases)):
+        gemms = [x for x in launches if "gemm_stream_bf16" in x[0]]
+        assert len(gemms) == 4
+        for x in gemms:
+            plan = dard.dard_gemm_plan(x[5], x[6], x[7], partial=x[4] in (RESID, PARTIAL))
+            nw = int(re.search(r"gemm_stream_bf16ILi(\d+)E", x[0]).group(1))
+            assert (nw, x[2]) == (plan[2], plan[3]), (M, d, F, x, plan)
