@@ -93,8 +93,8 @@ __device__ __forceinline__ floatx4 mfma16x16x4f(float a, float b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Four floats from an address that is only 4-byte aligned (the fp32 entry points
-// take any float pointer): one 16-byte load all the same.
+// Four floats at an address that is only 4-byte aligned (the fp32 entry points
+// take any float pointer): one 16-byte access all the same.
 __device__ __forceinline__ floatx4 ld_f4(const float* p) {
     typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
     return *reinterpret_cast<const f4u*>(p);

@@ -121,7 +121,9 @@ __device__ __forceinline__ float4 epi_fetch(const EpiArgs& e, int m, int n) {
 
 template <typename T, int EK>
 __device__ __forceinline__ void epi_store(const EpiArgs& e, int m, int n, floatx4 v, float4 f) {
-    if constexpr (EK == EPI_STORE_F32 || EK == EPI_PARTIAL) {
+    if constexpr (EK == EPI_STORE_F32) {
+        st_f4(e.y + (size_t)m * e.ldy + n, v);     // (dard_linear takes any float pointer)
+    } else if constexpr (EK == EPI_PARTIAL) {
         *reinterpret_cast<float4*>(e.y + (size_t)m * e.ldy + n) = make_float4(v[0], v[1], v[2], v[3]);
     } else if constexpr (EK == EPI_RESID) {
         *reinterpret_cast<float4*>(e.y + (size_t)m * e.ldy + n) =
@@ -134,9 +136,9 @@ __device__ __forceinline__ void epi_store(const EpiArgs& e, int m, int n, floatx
         // a listed row of the LM head: stored at its logit row when its code says so
         const int code = e.rowmap[m];
         const size_t o = (size_t)(code & kLmRowMask) * e.ldy + n;
-        const float4 val = make_float4(v[0], v[1], v[2], v[3]);
-        if ((code & kLmStore) || e.store_all) *reinterpret_cast<float4*>(e.y + o) = val;
-        if (e.y2) *reinterpret_cast<float4*>(e.y2 + o) = val;
+        if ((code & kLmStore) || e.store_all)
+            *reinterpret_cast<float4*>(e.y + o) = make_float4(v[0], v[1], v[2], v[3]);
+        if (e.y2) st_f4(e.y2 + o, v);              // (a captured-logits buffer off 16-byte alignment)
     } else if constexpr (EK == EPI_QKV) {
         const QkvRow row = qkv_row(e, m);
         const int qd = e.Hq * e.dh, kd = e.Hkv * e.dh;
