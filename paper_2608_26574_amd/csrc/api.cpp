@@ -738,7 +738,8 @@ int step_tail(const Fwd& f, const dard_params* params, int b, int B, const void*
         EpiArgs e{};
         e.kind = EPI_LMHEAD; e.y = logits; e.ldy = V; e.rowmap = rm; e.rows_dev = count;
         e.y2 = dbg && !direct ? dbg->logits : nullptr;
-        e.store_all = direct;
+        // captured logits and current-token probabilities are read from the stored rows
+        e.store_all = direct || (dbg && dbg->pcur_s);
         if (fused) { e.lpart = lpart; e.ntile = (V + tile_cols - 1) / tile_cols; }
         HIPOK(launch_gemm(dt, hx, max_rows, D, D, head_w, V, e, DARD_K_GEMM_HEAD, f.s, frag_rows(dt, max_rows)));
         if (fused) {

@@ -74,8 +74,8 @@ struct EpiArgs {
     // LMHEAD: the rows are listed rows (rowmap codes); rows at or past the
     // device count *rows_dev are skipped (row tiles entirely past it exit
     // before their K loop).  Stored rows go to y (ldy = V) at their logit
-    // row (with store_all every listed row), every row also to y2 when it is
-    // set (debug capture); with lpart the tiled kernel writes per-column-tile
+    // row (with store_all every listed row: debug captures), every row also to
+    // y2 when it is set; with lpart the tiled kernel writes per-column-tile
     // (max, argmax, sum) partials [M][ntile][3] of every row instead of
     // needing its logits.
     const int32_t* rowmap;

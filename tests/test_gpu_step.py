@@ -373,3 +373,32 @@ def test_fp8_kv_cache(case):
         assert excl <= state.size // 4
     else:
         check_workload_decisions(tok, state, got, ref, prm, f"fp8 kv {case['name']}")
+
+
+@pytest.mark.parametrize("b,B,flags", [(1, 24, 0), (3, 24, 0), (2, 80, 0), (5, 64, O.F_HIDDEN_MIX)])
+def test_captured_current_token_probability(b, B, flags):
+    """dbg->pcur_s in every form of the LM head (all rows, listed rows, and from 256
+    rows on fused partials, where the logits of C and U positions are stored only
+    for it), with the logits captured beside it and without: exp(l - max) / sum of
+    the captured shadow row."""
+    announce("captured pcur_s", b, B, flags)
+    dims = synth.Dims(1, 512, 4, 2, 128, 512, 1040, 512, "bf16")
+    w = {k: v.cuda() for k, v in sharpen(synth.make_weights(dims, seed=3), 8.0).items()}
+    eng = dard.Engine(dims, w, b, B, 40 + 2 * B)
+    eng.dard_prefill(dev(synth.prompt_ids(b, 40, dims.vocab, seed=4)))
+    tok, state, conf = synth.tiny_block(b, B, dims.vocab, seed=5)
+    prm = cparams(dard, P(dims.mask_id, flags))
+    got = []
+    for keys in (("pcur_s", "logits"), ("pcur_s",)):
+        eng.ws.zero_()
+        out, dbg = step_buffers(b, B, dims.vocab)
+        eng.dard_step(40, prm, dev(tok), dev(state), dev(conf), out["tok_out"], out["state_out"], out["conf_out"],
+                      out["block_done"], debug={k: dbg[k] for k in keys})
+        torch.cuda.synchronize()
+        got.append({k: dbg[k].cpu().numpy() for k in keys})
+    row = got[0]["logits"][:, B:].astype(np.float64)
+    row = np.exp(row - row.max(-1, keepdims=True))
+    ref = np.take_along_axis(row, tok[..., None].astype(np.int64), -1)[..., 0] / row.sum(-1)
+    cu = state != O.STATE_M
+    for g in got:
+        assert np.all(np.abs(g["pcur_s"][cu] - ref[cu]) <= 1e-5 * ref[cu] + 1e-30)
