@@ -724,6 +724,7 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
     const int si = a.masked ? st[i] : 0;
     const float ci = a.masked ? cf[i] : 0.f;
     float m = -INFINITY, l = 0.f;
+    bool seen = false;                             // a key that the row sees is among this lane's
     for (int k0 = wave * kKeysF; k0 < a.nkeys; k0 += kWavesF * kKeysF) {
         const bool sh = k0 < a.P_sh;               // (P_sh % 64 == 0: whole tiles)
         const float* kk = sh ? kb_sh : kb;
@@ -774,12 +775,15 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
         mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
         mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
         const float alpha = m == -INFINITY ? 0.f : expf(m - mt);
+        // (scores of minus infinity only so far: no weight, whatever other tiles hold)
+        const float base = mt == -INFINITY ? 0.f : mt;
+        seen |= vis != 0;
         float ps = 0.f;
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float p = (vis >> (4 * b + e)) & 1u ? expf(sc[b][e] - mt) : 0.f;
+                const float p = (vis >> (4 * b + e)) & 1u ? expf(sc[b][e] - base) : 0.f;
                 sc[b][e] = p;
                 ps += p;
             }
@@ -818,7 +822,9 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
             }
         }
     }
-    // l holds this lane's keys only: sum over the row's four lanes
+    // l holds this lane's keys only: sum over the row's four lanes.  Where every
+    // score is minus infinity the softmax is not a number, which l carries
+    if (m == -INFINITY && seen) l = NAN;
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     __shared__ floatx4 po[kWavesF][NC][64];
@@ -833,10 +839,11 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
     float f[kWavesF], lt = 0.f;
 #pragma unroll
     for (int w = 0; w < kWavesF; ++w) {
-        f[w] = pm[w][lr] == -INFINITY ? 0.f : expf(pm[w][lr] - mm);
-        lt += pl[w][lr] * f[w];
+        const bool none = pm[w][lr] == -INFINITY;  // (of this wave's keys; of all of them when mm says so)
+        f[w] = none ? 0.f : expf(pm[w][lr] - mm);
+        lt += none ? (mm == -INFINITY ? pl[w][lr] : 0.f) : pl[w][lr] * f[w];
     }
-    const float inv = lt > 0.f ? 1.f / lt : 0.f;
+    const float inv = lt > 0.f ? 1.f / lt : lt;    // 0 for a row without keys
     if (!row_ok) return;
     float* out = reinterpret_cast<float*>(a.out) + t * DH;
     for (int c = wave; c < NC; c += kWavesF) {

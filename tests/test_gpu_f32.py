@@ -87,3 +87,35 @@ def test_attention_f32_edges(b, B, P, Hq, Hkv, dh, unseen):
                 else:
                     # scores, probabilities and sums in fp32: a few 2^-24 of values of order one
                     assert (got[s, r, h] - ref).abs().max() < 1e-5, (s, r, h)
+
+
+@pytest.mark.parametrize("B,P", [(1, 0), (7, 160), (24, 101)])
+def test_attention_f32_infinite_scores(B, P):
+    """Keys whose score is minus infinity take no weight, also where a whole key
+    tile holds nothing else; a row that sees only such keys has no softmax (NaN)."""
+    announce("attention f32, scores of minus infinity", B, P)
+    b, Hq, dh, n = 2, 2, 64, P + 2 * B
+    g = torch.Generator().manual_seed(B + P)
+    q, k, v = torch.randn(b, 2 * B, Hq, dh, generator=g), torch.randn(b, Hq, n, dh, generator=g), \
+        torch.randn(b, Hq, dh, n, generator=g)
+    q[..., 0] = q[..., 0].abs() + 0.1
+    if P:
+        k[0, :, 32:P, 0] = -float("inf")       # whole tiles of the first sequence ...
+    k[1, :, :, 0] = -float("inf")              # ... and every key of the second
+    # all positions U: a row reads every x key (a shadow row its own shadow key instead)
+    state = np.full((b, B), O.STATE_U, dtype=np.uint8)
+    conf = np.full((b, B), 0.95, dtype=np.float32)
+    see = torch.ones(2 * B, n, dtype=torch.bool)
+    see[:, P + B:] = False
+    for i in range(B):
+        see[B + i, P + i], see[B + i, P + B + i] = False, True
+    out = torch.zeros(b, 2 * B, Hq, dh, device="cuda")
+    dard.dard_masked_attention(q.cuda(), k.cuda(), v.cuda(), P, torch.from_numpy(state).cuda(),
+                               torch.from_numpy(conf).cuda(), dh ** -0.5, 0, out)
+    torch.cuda.synchronize()
+    sc = torch.matmul(q.double().transpose(1, 2), k.double().transpose(-1, -2).contiguous()) * dh ** -0.5
+    p = torch.softmax(sc.masked_fill(~see, -float("inf")), -1)
+    ref = torch.matmul(p, v.double().transpose(-1, -2).contiguous()).transpose(1, 2)
+    assert torch.isnan(out[1]).all() and torch.isnan(ref[1]).all()
+    # scores, probabilities and sums in fp32: a few 2^-24 of values of order one
+    assert (out[0].cpu().double() - ref[0]).abs().max() < 1e-5
