@@ -355,13 +355,12 @@ hipError_t launch_resid_norm(int dtype, float* h, const float* part, int nsplit,
     if (frag && !frag_rows(dtype, rows)) return hipErrorInvalidValue;
     const size_t stride = (size_t)rows * d;
     if (nsplit < 0 || nsplit > 8 || d > 512 * 4 * kVec) return hipErrorInvalidValue;
-    if (dtype == DARD_DTYPE_BF16 && rows >= kManyRows && nsplit <= 2 && d <= 4096) {
+    if (dtype == DARD_DTYPE_BF16 && rows >= kManyRows && (nsplit == 0 || nsplit == 2) && d <= 4096) {
         const dim3 grid((rows + kRowWaves - 1) / kRowWaves), blk(64 * kRowWaves);
 #define DARD_RR(NS)                                                                                                   \
     launch((resid_norm_rows_kernel<bf16_t, NS, 16>), grid, blk, 0, s, h, part, stride, (const bf16_t*)gain, rows, d, \
            eps, (bf16_t*)xn, (int)frag)
         if (nsplit == 0) DARD_RR(0);
-        else if (nsplit == 1) DARD_RR(1);
         else DARD_RR(2);
 #undef DARD_RR
         return hipGetLastError();
