@@ -461,10 +461,11 @@ dard_status dard_linear(int dtype, const void* X, int M, int K, const void* Wp, 
  * plan[3] ways, with 1 the full sum on that tile); step
  * and prefill activations are fragment-major (frag_x != 0), dard_linear's
  * row-major (frag_x = 0).  plan: host int32 [4]. */
-#define DARD_GEMM_STREAM 0
-#define DARD_GEMM_PIPE   1
-#define DARD_GEMM_BIG    2
-#define DARD_GEMM_TILED  3
+#define DARD_GEMM_STREAM 0   /* weight streaming, at most 64 rows                     */
+#define DARD_GEMM_PIPE   1   /* the tiled kernel at 65 to 255 rows (K split up to 8   */
+                             /* ways; the name is that of the kernel it replaced)     */
+#define DARD_GEMM_BIG    2   /* the tiled kernel from 256 rows (K split up to 4 ways) */
+#define DARD_GEMM_TILED  3   /* row-major activations, 128 x 128                      */
 #define DARD_GEMM_F32    4
 dard_status dard_gemm_plan(int dtype, int M, int N, int K, int partial, int frag_x, int32_t* plan);
 

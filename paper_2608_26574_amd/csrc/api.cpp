@@ -651,10 +651,11 @@ namespace {
 //     candidates' shadow rows first, then, once their verification has given
 //     the guidance weights, the U shadow rows and one mixed row per M
 //     position: B rows per sequence.
-//   - When the large-tile GEMM runs the head (and neither the entropy /
-//     margin statistics nor the current-token probability are asked for),
-//     its epilogue forms the (max, argmax, sum) partials of the C and U
-//     shadow rows itself and their logits are never written.
+//   - From kFusedHeadRows listed rows in bf16 (and when neither the entropy /
+//     margin statistics nor verification by the current token's probability are
+//     asked for) the head's epilogue forms the (max, argmax, sum) partials of
+//     the C and U shadow rows itself, and their logits are written only for
+//     debug captures.
 int step_tail(const Fwd& f, const dard_params* params, int b, int B, const void* xrows, const int32_t* tok_in,
               const uint8_t* state_in, int32_t* tok_out, uint8_t* state_out, float* conf_out, int32_t* block_done,
               const dard_step_debug* dbg) {
@@ -718,7 +719,7 @@ int step_tail(const Fwd& f, const dard_params* params, int b, int B, const void*
         return DARD_OK;
     }
 
-    const bool fused = dt == DARD_DTYPE_BF16 && plan[0] == DARD_GEMM_BIG && !stats &&
+    const bool fused = dt == DARD_DTYPE_BF16 && max_rows >= kFusedHeadRows && !stats &&
                        !(flags & DARD_F_VERIFY_PCUR);
     int32_t* rm0 = (int32_t*)(f.ws + f.W.rowmap);
     int32_t* rm1 = rm0 + rows;

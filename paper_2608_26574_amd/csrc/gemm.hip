@@ -968,7 +968,7 @@ hipError_t launch_gemm(int dtype, const void* X, int M, int K, int ldx, const vo
                        const EpiArgs& e, int kernel_class, hipStream_t s, bool xfrag) {
     TraceScope ts(kernel_class, s);
     if (e.kind == EPI_LMHEAD && (!e.rowmap || !e.rows_dev || !e.y)) return hipErrorInvalidValue;
-    // fused LM-head partials: only the large-tile kernel forms them
+    // fused LM-head partials: only the tiled kernel forms them
     if (e.kind == EPI_LMHEAD && e.lpart && (dtype != DARD_DTYPE_BF16 || M <= 64 || !xfrag))
         return hipErrorInvalidValue;
     if (dtype == DARD_DTYPE_F32) {

@@ -68,6 +68,10 @@ constexpr int kLmStore = 1 << 24;   // stored at the logit row
 constexpr int kLmToV = 1 << 25;     // merged partial of a candidate's shadow row (verification)
 constexpr int kLmToM = 1 << 26;     // merged partial of a U shadow row or of a mixed M row
 constexpr int kLmMix = 1 << 27;     // the row is w x + (1 - w) s of an M position (hidden-state mixing)
+// Listed rows of an LM-head pass from which its epilogue forms the confidence
+// partials of the C and U rows.  The tiled kernel could do so from 65 rows; below
+// 256, where it has not been timed, their logits are stored and read back.
+constexpr int kFusedHeadRows = 256;
 
 struct EpiArgs {
     int kind;

@@ -109,7 +109,7 @@ def test_dims_validation_and_sizes():
     bad = dard.make_dims(synth.Dims(2, 4096, 32, 32, 128, 12288, 126460, 64, "bf16"))
     assert L.dard_packed_weight_bytes(ctypes.byref(bad)) == 0
     # a bf16 weight matrix of 4 GiB or more (LM head 262144 x 8192) is refused:
-    # the pipelined GEMM addresses weights with 32-bit byte offsets
+    # the tiled GEMM addresses weights with 32-bit byte offsets
     bad = dard.make_dims(synth.Dims(2, 8192, 64, 8, 128, 28672, 262144, 64, "bf16"))
     assert L.dard_packed_weight_bytes(ctypes.byref(bad)) == 0
     assert b"4 GiB" in L.dard_last_error()
@@ -139,12 +139,13 @@ def test_gemm_plan_query():
     # decoding step rows: the weight-streaming kernel; O / down split K
     assert dard.dard_gemm_plan(64, 24576, 4096)[0] == dard.GEMM_STREAM
     assert dard.dard_gemm_plan(64, 4096, 12288, partial=True)[3] > 1
-    # 64 < M < 256: the pipelined kernel; M >= 256: the large tiles
+    # 64 < M < 256 and M >= 256: the tiled kernel under its two codes
     assert dard.dard_gemm_plan(144, 1024, 512)[0] == dard.GEMM_PIPE
     assert dard.dard_gemm_plan(1024, 37888, 3584)[0] == dard.GEMM_BIG
     # a 700-row prefill of a wide FFN fills whole rounds with 128 x 192 tiles
     assert dard.dard_gemm_plan(700, 16256, 320)[:3] == (dard.GEMM_BIG, 4, 6)
-    # split-K partial epilogues never take the 128 x 192 tile
+    # the residual projection of those sizes takes another one (below 4096 rows
+    # split-K partials never run on 128 x 192; this one runs unsplit on 256 x 192)
     assert dard.dard_gemm_plan(700, 16256, 320, partial=True)[1:3] != (4, 6)
     # row-major activations (dard_linear) and fp32
     assert dard.dard_gemm_plan(300, 256, 128, frag_x=False)[0] == dard.GEMM_TILED

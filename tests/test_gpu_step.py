@@ -153,10 +153,10 @@ def test_tiny_step_fp32_transitions(flags, wf):
 @pytest.mark.parametrize("case", [
     dict(d=256, H=4, Hkv=4, dh=64, F=512, V=4096, b=2, B=16, P=40, L=2),
     dict(d=512, H=4, Hkv=2, dh=128, F=1024, V=2048, b=1, B=7, P=3, L=2),
-    dict(d=512, H=4, Hkv=1, dh=128, F=512, V=1024, b=3, B=24, P=50, L=1),   # 144 rows: pipelined GEMMs
+    dict(d=512, H=4, Hkv=1, dh=128, F=512, V=1024, b=3, B=24, P=50, L=1),   # 144 rows: tiled GEMMs below 256 rows
     dict(d=512, H=8, Hkv=8, dh=64, F=1024, V=2048, b=1, B=20, P=60, L=2),    # 40 and 60 rows: ragged last block
-    dict(d=256, H=4, Hkv=2, dh=64, F=512, V=1024, b=1, B=16, P=300, L=2),    # 300 prefill rows: 128 x 128 large tiles
-    dict(d=256, H=4, Hkv=2, dh=64, F=512, V=1024, b=4, B=16, P=1030, L=1),   # 4120 prefill rows: 128 x 256 large tiles
+    dict(d=256, H=4, Hkv=2, dh=64, F=512, V=1024, b=1, B=16, P=300, L=2),    # 300 prefill rows: 64 x 64 tiles
+    dict(d=256, H=4, Hkv=2, dh=64, F=512, V=1024, b=4, B=16, P=1030, L=1),   # 4120 prefill rows
     dict(d=320, H=5, Hkv=5, dh=64, F=576, V=1040, b=1, B=12, P=300, L=1),    # ragged last column tile in every GEMM
     # 700 prefill rows (not a multiple of 128) and 2F = 16256 (not a multiple of
     # 192): the gate/up projection of the prefill takes the 128 x 192 tile, with a
@@ -312,7 +312,7 @@ def test_step_reports_bad_state_codes():
     dict(name="llada8b b1", dims=("llada8b", 2), b=1, B=32, P=256, frac=0.5, seed=12),
     # 7B GQA shape, batch 8: 512 rows per pass, the large-tile head with fused partials
     dict(name="dream7b b8", dims=("dream7b", 1), b=8, B=64, P=160, frac=0.3, seed=13),
-    # small bf16 model, 144 rows per pass: the pipelined head (a head
+    # small bf16 model, 144 rows per pass: the tiled head that stores its rows (a head
     # sharpened x12: its d = 512 leaves the x6 head's top probabilities below
     # tau_u).  Weights drawn on the host, where the oracle alone shows that
     # this step has 11 C->U and 10 C->M decisions (none at scale 10)
