@@ -691,6 +691,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
 // (row, head) walking every key took 876 us at 64 rows x 4 heads, 128 keys: a
 // serial chain in 4 workgroups; this takes 11 us.
 constexpr int kWavesF = 4, kKeysF = 32;
+constexpr size_t kMaxWgsF = size_t(1) << 23;   // workgroups of a launch
 
 template <int DH>
 __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
@@ -963,12 +964,29 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
         return hipGetLastError();
     }
     if (a.kv_fp8) return hipErrorInvalidValue;   // the fp8 cache is a bf16-model variant
-    const size_t wgs = (size_t)((a.R + 15) / 16) * a.Hq * a.b;
-    if (wgs > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)wgs), block(64 * kWavesF);
-    if (a.dh == 128) launch(attn_f32_kernel<128>, grid, block, 0, s, a);
-    else launch(attn_f32_kernel<64>, grid, block, 0, s, a);
-    return hipGetLastError();
+    // a launch holds fewer than 2^32 threads: very many sequences take several
+    const size_t per_seq = (size_t)((a.R + 15) / 16) * a.Hq;
+    if (per_seq > kMaxWgsF) return hipErrorInvalidValue;
+    const int most = (int)std::min<size_t>(a.b, kMaxWgsF / per_seq);
+    for (int s0 = 0; s0 < a.b; s0 += most) {
+        AttnArgs c = a;
+        const size_t qo = (size_t)s0 * a.R * a.Hq * a.dh, ko = (size_t)s0 * a.Hkv * a.cap * a.dh;
+        c.b = std::min(most, a.b - s0);
+        c.q = reinterpret_cast<const float*>(a.q) + qo;
+        c.out = reinterpret_cast<float*>(a.out) + qo;
+        c.k = reinterpret_cast<const float*>(a.k) + ko;
+        c.v = reinterpret_cast<const float*>(a.v) + ko;
+        if (a.masked) {
+            c.state = a.state + (size_t)s0 * a.B;
+            c.conf = a.conf + (size_t)s0 * a.B;
+        }
+        const dim3 grid((unsigned)(per_seq * c.b)), block(64 * kWavesF);
+        if (a.dh == 128) launch(attn_f32_kernel<128>, grid, block, 0, s, c);
+        else launch(attn_f32_kernel<64>, grid, block, 0, s, c);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace dard

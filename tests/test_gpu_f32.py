@@ -119,3 +119,21 @@ def test_attention_f32_infinite_scores(B, P):
     assert torch.isnan(out[1]).all() and torch.isnan(ref[1]).all()
     # scores, probabilities and sums in fp32: a few 2^-24 of values of order one
     assert (out[0].cpu().double() - ref[0]).abs().max() < 1e-5
+
+
+def test_attention_f32_very_many_sequences():
+    """More rows of heads than one launch takes (2^23 workgroups): blocks of one
+    position and no prefix, where a U token's x row reads its own x key and its
+    shadow row its shadow key, so that every row is one of the V vectors."""
+    b, Hq, dh = (1 << 19) + 3, 32, 64          # 2^32 threads in one launch; 8.6 GB of queries
+    announce("attention f32, sequences", b)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q = torch.randn(b, 2, Hq, dh, generator=g, device="cuda")
+    k = torch.randn(b, 1, 2, dh, generator=g, device="cuda")
+    v = torch.randn(b, 1, dh, 2, generator=g, device="cuda")
+    state = torch.full((b, 1), O.STATE_U, dtype=torch.uint8, device="cuda")
+    conf = torch.full((b, 1), 0.95, device="cuda")
+    out = torch.zeros_like(q)
+    dard.dard_masked_attention(q, k, v, 0, state, conf, dh ** -0.5, 0, out)
+    ref = v.transpose(2, 3)[:, 0, :, None].expand(b, 2, Hq, dh)
+    assert torch.equal(out, ref)
