@@ -307,13 +307,14 @@ __global__ __launch_bounds__(64 * KSPLIT) void gemm_stream_bf16(const bf16_t* __
 // 4 WM waves (WM x 4) owns a (16 TI WM)-token x (64 TJ)-column output tile; wave
 // (wm, wn) computes 16 TI tokens x 16 TJ columns.
 // What bounds such a tile is the traffic behind the MFMAs.  With both operands
-// staged in LDS a 256 x 128 tile moved 72 KB through LDS per 512 MFMA cycles of
-// the CU (128 bytes per cycle), more than the MFMAs leave time for.  Here only
+// staged in LDS a 256 x 128 tile moved 72 KB through LDS (copies in and operand
+// reads) per 512 MFMA cycles of the CU, 144 bytes per cycle where LDS serves 128.  Here only
 // X, which the four column waves share, goes through LDS (copied straight from
 // global memory, NST 64-wide k units deep); a wave's weight blocks are its own,
 // and fragment-major weights already are MFMA operands, so they are loaded into
 // registers WD (two to four) units ahead and never touch LDS.  A 128 x 192 tile then moves
-// 40 KB through LDS per 768 MFMA cycles, its barrier is one per 64-wide unit,
+// 80 KB through LDS per 768 MFMA cycles (16 in, and 16 read by each of four waves:
+// 107 bytes per cycle, still near that limit), its barrier is one per 64-wide unit,
 // and three workgroups share a CU, so one's prologue, epilogue and barrier
 // waits lie under the others' MFMAs.
 // Measured on MI355X (8192 x 37888 x 3584, SwiGLU): 2160 us (1030 TFLOP/s) with
@@ -850,8 +851,10 @@ StreamCfg stream_cfg(int N, int K, bool partial) {
 // fixed part for prologue and epilogue), and reads the weights from HBM for
 // 2 N K bytes / 5 TB/s + 4 us; the shorter of the two hides but for a third.
 // Rates and fixed parts are fitted to a sweep on MI355X of 72 to 2048 rows over
-// the projections of the 8B and 7B shapes, weights cold in cache (140 shapes; the
-// pick is within 2 % of the best tile on average).  No tile is best everywhere:
+// the projections of the 8B and 7B shapes, weights cold in cache (136 shapes; the
+// pick is within 2 % of the best tile on average, and 17 % off at worst, 2048 x 4608 x
+// 3584, where epilogues but the residual's leave the best one out).  No tile is best
+// everywhere:
 // 192 x 24576 x 4096 takes 55 us with 192 x 128 (71 with 128 x 128), 128 x 12288 x
 // 4096 35 us with 96 x 128 (44 with 128 x 128), 96 x 4608 x 3584 18 us with 64 x 64
 // (32 with 128 x 128), 1024 x 37888 x 3584 231 us with 128 x 192 (260 with 128 x
@@ -912,10 +915,14 @@ BigCfg big_cfg(int M, int N, int K, bool resid, int max_split, bool fused_head) 
 }
 
 // Rows that an LM-head launch over at most M listed rows is tiled for.  The count
-// is device data: with logit mixing between M / 2 (no masked position) and M, so
-// three quarters.  Tiling for M gave a block of 128 (176 listed rows of 256) two
-// 128-row tiles and a second pass over the weights: 350 us, 276 us with one of 192.
-int head_rows(int M) { return (3 * M + 3) / 4; }
+// is device data: with logit mixing M at the first step of a block (every position
+// masked), toward M / 2 at its end.  Up to 192 rows one row tile can hold any count
+// and M it is: tiled for three quarters, 128 rows of the 8B head took 293 us with all
+// of them listed and 224 to 231 with up to three quarters, tiled for M 244 and 231 to
+// 238.  Above, three quarters: 256 rows take 260 to 263 us in one tile of 192 rows up
+// to there and 360 in two beyond, 324 to 339 us throughout when tiled for M; from 320
+// rows the two rarely differ.
+int head_rows(int M) { return M <= 192 ? M : (3 * M + 3) / 4; }
 
 // The tile of one launch of the M > 64 kernel; the split of a residual projection
 // (EPI_PARTIAL) is the one whose time is least, and where that is 1 the full sum

@@ -35,29 +35,45 @@ int hipExtLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t lds, v
 int hipGetLastError(void) { return 0; }
 """
 
-# one prefill of one layer per line of the input: rows, d, ffn
+# one prefill of one layer per line of the input (rows, d, ffn), or one step of no
+# layer (sequences, block, d, vocabulary)
 PROGRAM = r"""
 import ctypes, sys
 ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
 L = ctypes.CDLL(sys.argv[2])
 L.dard_workspace_bytes.restype = ctypes.c_size_t
 fake = ctypes.c_void_p(1 << 20)
+class Params(ctypes.Structure):
+    _fields_ = [("tau_c", ctypes.c_float), ("tau_u", ctypes.c_float), ("lambda_", ctypes.c_double),
+                ("p0", ctypes.c_double), ("mask_id", ctypes.c_int32), ("flags", ctypes.c_uint32),
+                ("w_fixed", ctypes.c_float)]
 for line in sys.stdin:
-    M, d, F = map(int, line.split())
-    dims = (ctypes.c_int32 * 12)(1, d, d // 128, max(1, d // 256), 128, F, 1040, 1 << 20, 1)
+    v = list(map(int, line.split()))
+    step = len(v) == 4
+    d, F, V = (v[2], 64, v[3]) if step else (v[1], v[2], 1040)
+    dims = (ctypes.c_int32 * 12)(0 if step else 1, d, d // 128, max(1, d // 256), 128, F, V, 1 << 20, 1)
     ctypes.cast(dims, ctypes.POINTER(ctypes.c_float))[10] = 1e4
-    ws = L.dard_workspace_bytes(dims, 1, 1, M + 2)
-    rc = L.dard_prefill(dims, fake, fake, M + 2, 1, M, fake, None, fake, ctypes.c_size_t(ws), None)
+    if step:
+        b, B = v[:2]
+        params = Params(0.4, 0.9, 0.5, 0.1, V - 1, 0, 0.0)
+        ws = L.dard_workspace_bytes(dims, b, B, 2 * B)
+        rc = L.dard_step(dims, fake, fake, 2 * B, 0, ctypes.byref(params), b, B, *[fake] * 7, None, fake,
+                         ctypes.c_size_t(ws), None)
+    else:
+        M = v[0]
+        ws = L.dard_workspace_bytes(dims, 1, 1, M + 2)
+        rc = L.dard_prefill(dims, fake, fake, M + 2, 1, M, fake, None, fake, ctypes.c_size_t(ws), None)
     ctypes.CDLL(None).fflush(None)
     print("end", rc, flush=True)
 """
 
-STORE, RESID, SWIGLU, QKV, PARTIAL = range(5)
+STORE, RESID, SWIGLU, QKV, PARTIAL, LMHEAD = range(6)
 
 
 @pytest.fixture(scope="module")
-def prefills(tmp_path_factory):
-    """cases [(M, d, F)] -> per case the launches (kernel, grid x, y, threads, kind, M, N, K)."""
+def forwards(tmp_path_factory):
+    """cases, prefills (M, d, F) or steps (b, B, d, V) -> per case the launches
+    (kernel, grid x, y, threads, kind, M, N, K)."""
     folder = tmp_path_factory.mktemp("standin")
     src, so = folder / "standin.c", folder / "standin.so"
     src.write_text(STAND_IN)
@@ -65,7 +81,8 @@ def prefills(tmp_path_factory):
 
     def run(cases):
         r = subprocess.run([sys.executable, "-c", PROGRAM, str(so), os.path.abspath(dard.LIB_PATH)],
-                           input="".join("%d %d %d\n" % c for c in cases), capture_output=True, text=True, timeout=120)
+                           input="".join(" ".join(map(str, c)) + "\n" for c in cases), capture_output=True, text=True,
+                           timeout=120)
         assert r.returncode == 0, r.stderr
         out, cur = [], []
         for line in r.stdout.splitlines():
@@ -96,9 +113,9 @@ CASES = [(M, d, F) for d, F in ((4096, 12288), (3584, 18944), (1024, 4160))
                    16000)] + [(700, 8192, 320), (700, 512, 128)]
 
 
-def test_tiles_that_run_are_the_tiles_of_the_plan(prefills):
+def test_tiles_that_run_are_the_tiles_of_the_plan(forwards):
     full_256 = 0
-    for (M, d, F), launches in zip(CASES, prefills(CASES)):
+    for (M, d, F), launches in zip(CASES, forwards(CASES)):
         gemms = [x for x in launches if "gemm_big_bf16" in x[0]]
         assert len(gemms) == 4, (M, d, F, launches)   # QKV, O, gate/up, down
         for x, (N, K, kinds) in zip(gemms, (((d // 128 + 2 * max(1, d // 256)) * 128, d, (QKV,)), (d, d, (RESID, PARTIAL)),
@@ -111,12 +128,34 @@ def test_tiles_that_run_are_the_tiles_of_the_plan(prefills):
     assert full_256 >= 3   # the full sums on 256 x 192 tiles are among the cases
 
 
-def test_streaming_tiles_that_run_are_the_tiles_of_the_plan(prefills):
+def test_streaming_tiles_that_run_are_the_tiles_of_the_plan(forwards):
     cases = [(M, d, F) for M in (1, 17, 64) for d, F in ((512, 1088), (4096, 12288), (384, 512), (1024, 960))]
-    for (M, d, F), launches in zip(cases, prefills(cases)):
+    for (M, d, F), launches in zip(cases, forwards(cases)):
         gemms = [x for x in launches if "gemm_stream_bf16" in x[0]]
         assert len(gemms) == 4
         for x in gemms:
             plan = dard.dard_gemm_plan(x[5], x[6], x[7], partial=x[4] in (RESID, PARTIAL))
             nw = int(re.search(r"gemm_stream_bf16ILi(\d+)E", x[0]).group(1))
             assert (nw, x[2]) == (plan[2], plan[3]), (M, d, F, x, plan)
+
+
+# listed rows (b * 2B) on both sides of every tile height
+HEADS = [(2, 18), (3, 16), (2, 25), (2, 32), (3, 22), (2, 36), (5, 16), (3, 32), (7, 16), (4, 32), (3, 64), (16, 32),
+         (8, 64)]
+
+
+@pytest.mark.parametrize("d,V", [(4096, 126464), (3584, 152064), (512, 2048)])
+def test_lm_head_holds_every_count_in_one_row_tile_up_to_192_rows(forwards, d, V):
+    """The number of rows that the head runs over is known on the device only; at
+    the first step of a block it is all of them."""
+    for (b, B), launches in zip(HEADS, forwards([(b, B, d, V) for b, B in HEADS])):
+        heads = [x for x in launches if "gemm_big_bf16" in x[0]]
+        assert len(heads) == 1 and heads[0][4:] == [LMHEAD, 2 * b * B, V, d], launches
+        ti, tj, split = tile(heads[0])
+        row_tiles, col_tiles = -(-2 * b * B // (32 * ti)), -(-V // (32 * tj))
+        assert heads[0][1] == row_tiles * col_tiles and split == 1
+        if 2 * b * B <= 192 and V > 100000:
+            assert row_tiles == 1, (b, B, ti, tj)
+        # partials come from the head's epilogue (tiles of 128 columns or more) from 256 rows
+        merges = [x for x in launches if "lm_merge_kernel" in x[0]]
+        assert len(merges) == (2 * b * B >= 256) and (not merges or tj >= 4)
