@@ -866,7 +866,9 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
 //   2 waves per workgroup (batch 16: 36 us); with few heads (batch 1-2), 4
 //   waves and key splits of about 3 tiles merged by the combine kernel
 //   (batch 1, prompt 736: 34 -> 20 us); in between (batch 4), no split and a
-//   second key group of 2 waves taking alternate tiles (43 -> 35 us).
+//   second key group of 2 waves taking alternate tiles (43 -> 35 us).  Two
+//   splits there gained nothing (96 workgroups, 535 keys: 27 us, split 28 us
+//   and 6 for the combine); other counts between 65 and 170 were not tried.
 struct AttnCfg {
     int waves, g, rowtiles, ns, tps;
 };

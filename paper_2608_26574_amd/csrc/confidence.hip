@@ -4,8 +4,9 @@
 // workgroup reduces one chunk with 16-byte loads into a partial
 // (max, first argmax, sum of exp(l - max)), so that even a single step's few
 // rows fill the chip.  Partials are merged in an order that the chunk count
-// fixes, which keeps the result independent of scheduling.  Mixed rows are formed on the fly,
-// (w * l_x) + ((1 - w) * l_s) with every operation rounded once in fp32.
+// fixes, which keeps the result independent of scheduling.  Mixed rows are
+// formed on the fly, (w * l_x) + ((1 - w) * l_s) with every operation rounded
+// once in fp32.
 //
 // The statistics variant (entropy and margin orderings of Sec. 5.1) carries
 // two more terms in the same pass: t = sum exp(l - max) (l - max), so that

@@ -38,11 +38,6 @@ __device__ __forceinline__ void store_vec(T* p, const float (&v)[N]) {
     *reinterpret_cast<Vec*>(p) = x;
 }
 
-// The embedding row is held in registers between its load, the store to h and
-// the normalised store, in 16-byte pieces (an 8-element group of the
-// fragment-major layout is contiguous), so the row costs one read and two
-// writes: 64 rows of 4096 in 5.2 us, 640 rows in 10.6 us (15 and 27 us when h
-// was read back and values were stored one by one).
 // Source row of embedding row `row`; in_table is cleared for a row of `embeds`.
 template <typename T>
 __device__ __forceinline__ const T* embed_src(const int32_t* ids, const T* embeds, const T* table, size_t row, int d,
@@ -60,6 +55,11 @@ __device__ __forceinline__ const T* embed_src(const int32_t* ids, const T* embed
     return id >= 0 ? table + (size_t)id * d : embeds + row * d;
 }
 
+// The embedding row is held in registers between its load, the store to h and
+// the normalised store, in 16-byte pieces (an 8-element group of the
+// fragment-major layout is contiguous), so the row costs one read and two
+// writes: 64 rows of 4096 in 5.2 us, 640 rows in 10.6 us (15 and 27 us when h
+// was read back and values were stored one by one).
 template <typename T>
 __global__ __launch_bounds__(256) void embed_norm_kernel(const int32_t* __restrict__ ids, const T* __restrict__ embeds,
                                                          const T* __restrict__ table, const T* __restrict__ gain,
