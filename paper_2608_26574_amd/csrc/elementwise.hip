@@ -235,44 +235,28 @@ __global__ __launch_bounds__(512) void resid_norm_kernel(float* __restrict__ h, 
     }
 }
 
-// The same for many rows, a wave per row and eight adjacent rows per workgroup
-// (see embed_norm_rows_kernel).  8192 rows of 3584 without partials:
-// 61 -> 40 us; embedding them 98 -> 58 us.
-template <typename T, int NS, int IT>
-__global__ __launch_bounds__(64 * kRowWaves) void resid_norm_rows_kernel(float* __restrict__ h,
-                                                                         const float* __restrict__ part,
-                                                                         size_t split_stride,
+// The same for many rows without partials, a wave per row and eight adjacent rows
+// per workgroup (see embed_norm_rows_kernel).  8192 rows of 3584: 61 -> 40 us;
+// embedding them 98 -> 58 us.  Partials are left to a workgroup per row, whose
+// waves have more loads in flight: two of them at 2100 rows of 4096 take 35 us
+// there and 51 here, at 4000 rows 60 and 69.
+template <typename T, int IT>
+__global__ __launch_bounds__(64 * kRowWaves) void resid_norm_rows_kernel(const float* __restrict__ h,
                                                                          const T* __restrict__ gain, int rows, int d,
                                                                          float eps, T* __restrict__ xn, int frag) {
     const int lane = threadIdx.x & 63;
     const size_t row = (size_t)blockIdx.x * kRowWaves + (threadIdx.x >> 6);
     if (row >= (size_t)rows) return;
-    float* hr = h + row * d;
+    const float* hr = h + row * d;
     float4 v[IT];                                  // d <= 256 IT
+    float ss = 0.f;
 #pragma unroll
     for (int q = 0; q < IT; ++q) {
         const int c = 4 * (lane + 64 * q);
         v[q] = c < d ? *reinterpret_cast<const float4*>(hr + c) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const float* pr = part + s * split_stride + row * d;
-#pragma unroll
-        for (int q = 0; q < IT; ++q) {
-            const int c = 4 * (lane + 64 * q);
-            if (c < d) {
-                const float4 p = *reinterpret_cast<const float4*>(pr + c);
-                v[q].x += p.x; v[q].y += p.y; v[q].z += p.z; v[q].w += p.w;
-            }
-        }
-    }
-    float ss = 0.f;
-#pragma unroll
-    for (int q = 0; q < IT; ++q) {
-        const int c = 4 * (lane + 64 * q);
-        if (NS > 0 && c < d) *reinterpret_cast<float4*>(hr + c) = v[q];
-        ss += v[q].x * v[q].x + v[q].y * v[q].y + v[q].z * v[q].z + v[q].w * v[q].w;
-    }
+    for (int q = 0; q < IT; ++q) ss += v[q].x * v[q].x + v[q].y * v[q].y + v[q].z * v[q].z + v[q].w * v[q].w;
     const float inv = rsqrtf(wave_sum(ss) / (float)d + eps);
 #pragma unroll
     for (int q = 0; q < IT; ++q) {
@@ -321,7 +305,7 @@ hipError_t launch_pack_rows(const void* src0, const void* src1, void* dst, int n
     return hipGetLastError();
 }
 
-// Rows from which a wave per row fills the chip (rows of 3584 and 4096: at 1024
+// Rows from which a wave per row fills the chip (without partials; rows of 3584 and 4096: at 1024
 // rows 11.0 us against 9.1 with a workgroup per row, at 2048 16.2 against 18.5).
 constexpr int kManyRows = 2048;
 
@@ -355,14 +339,9 @@ hipError_t launch_resid_norm(int dtype, float* h, const float* part, int nsplit,
     if (frag && !frag_rows(dtype, rows)) return hipErrorInvalidValue;
     const size_t stride = (size_t)rows * d;
     if (nsplit < 0 || nsplit > 8 || d > 512 * 4 * kVec) return hipErrorInvalidValue;
-    if (dtype == DARD_DTYPE_BF16 && rows >= kManyRows && (nsplit == 0 || nsplit == 2) && d <= 4096) {
-        const dim3 grid((rows + kRowWaves - 1) / kRowWaves), blk(64 * kRowWaves);
-#define DARD_RR(NS)                                                                                                   \
-    launch((resid_norm_rows_kernel<bf16_t, NS, 16>), grid, blk, 0, s, h, part, stride, (const bf16_t*)gain, rows, d, \
-           eps, (bf16_t*)xn, (int)frag)
-        if (nsplit == 0) DARD_RR(0);
-        else DARD_RR(2);
-#undef DARD_RR
+    if (dtype == DARD_DTYPE_BF16 && rows >= kManyRows && nsplit == 0 && d <= 4096) {
+        launch((resid_norm_rows_kernel<bf16_t, 16>), dim3((rows + kRowWaves - 1) / kRowWaves), dim3(64 * kRowWaves), 0,
+               s, h, (const bf16_t*)gain, rows, d, eps, (bf16_t*)xn, (int)frag);
         return hipGetLastError();
     }
 #define DARD_RN(T, NS)                                                                                 \

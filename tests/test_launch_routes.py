@@ -139,6 +139,22 @@ def test_streaming_tiles_that_run_are_the_tiles_of_the_plan(forwards):
             assert (nw, x[2]) == (plan[2], plan[3]), (M, d, F, x, plan)
 
 
+def test_partials_are_added_by_a_workgroup_per_row(forwards):
+    """From 2048 rows a wave takes a row of the norms that add no partials; those
+    that add them keep a workgroup per row at every row count."""
+    cases = [(2047, 4096, 12288), (2048, 1024, 4160), (2100, 4096, 12288), (2304, 3584, 18944), (3584, 4096, 12288)]
+    split = 0
+    for (M, d, F), launches in zip(cases, forwards(cases)):
+        for x, norm in zip(launches, launches[1:]):
+            if "gemm_big_bf16" not in x[0] or x[4] not in (RESID, PARTIAL) or "norm" not in norm[0]:
+                continue
+            by_wave = x[4] == RESID and M >= 2048
+            assert ("resid_norm_rows_kernel" in norm[0]) == by_wave, (M, d, F, x, norm)
+            assert norm[1] == (-(-M // 8) if by_wave else M)
+            split += x[4] == PARTIAL and M >= 2048
+    assert split >= 2
+
+
 # listed rows (b * 2B) on both sides of every tile height
 HEADS = [(2, 18), (3, 16), (2, 25), (2, 32), (3, 22), (2, 36), (5, 16), (3, 32), (7, 16), (4, 32), (3, 64), (16, 32),
          (8, 64)]
