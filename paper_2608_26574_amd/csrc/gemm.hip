@@ -865,12 +865,16 @@ StreamCfg stream_cfg(int N, int K, bool partial) {
 // rows, at least 8 k units each; a split adds its partial's pass through the
 // residual-norm kernel, about 4.4 bytes per nanosecond.  One list of tiles serves
 // the decision, the partials and the full sum, so that what is priced is what runs.
-// From 4096 rows, where one split fills the chip, full sums leave 256 x 192 out (8192
-// x 3584 x 18944: 914 us with 128 x 192, 1034 with 256 x 192; a prefill of 8192 rows
-// was 1.6 % slower with it); below, partials leave 128 x 192 out and full sums gain
-// from 256 x 192 (2560 x 4096 x 12288: 221 us, 244 with 192 x 128).  Other epilogues
-// leave 256 x 192 out: inside a step 128 x 192 was faster there (1024 x 37888 x 3584:
-// 235 against 275 us), most of all for LM-head launches, whose row count the host
+// From 4096 rows, where one split fills the chip, full sums leave 256-row tiles out
+// (8192 x 3584 x 18944: 914 us with 128 x 192, 1034 with 256 x 192; a prefill of 8192
+// rows was 1.6 % slower with it); below, partials leave 128 x 192 out and full sums gain
+// from 256 x 192 (2560 x 4096 x 12288: 221 us, 244 with 192 x 128) and, where one round
+// of them covers the matrix, from 256 x 128 (2048 x 4096 x 4096: 71 us, 80 with 128 x
+// 128 two to a CU; 1920 x 4096 x 12288: 187 and 206; 2304 x 3584 x 18944: 284 and 289;
+// in a second round they lose, 3840 x 4096 x 12288: 364 us, 352 with 192 x 128, and their
+// fixed part is set so that a short K leaves them out, 3328 x 2048 x 1088: 28 us and 27;
+// with K = 2048 both take 40, with 8192 116 and 127).  Other epilogues leave 256 rows out: inside a step 128 x 192 was faster there (1024 x 37888 x
+// 3584: 235 against 275 us), most of all for LM-head launches, whose row count the host
 // does not know (320 of at most 1024 rows: 414 against 554 us); with fused partials
 // those take tiles of 128 columns or more, the merge's limit.
 struct BigCfg {
@@ -882,8 +886,8 @@ BigCfg big_cfg(int M, int N, int K, bool resid, int max_split, bool fused_head) 
         int ti, tj;
         double rate, fixed_us;   // multiply-adds per microsecond and CU in millions; per tile
     };
-    const Tile cand[7] = {{4, 6, 2.8, 5.0}, {6, 4, 2.8, 6.0}, {4, 4, 2.4, 4.0}, {3, 4, 2.0, 4.5},
-                          {4, 2, 1.6, 2.0}, {2, 2, 1.2, 1.0}, {8, 6, 2.85, 10.0}};
+    const Tile cand[8] = {{4, 6, 2.8, 5.0}, {6, 4, 2.8, 6.0}, {4, 4, 2.4, 4.0}, {3, 4, 2.0, 4.5},
+                          {4, 2, 1.6, 2.0}, {2, 2, 1.2, 1.0}, {8, 6, 2.85, 10.0}, {8, 4, 2.45, 8.5}};
     BigCfg best{0, 0, 1};
     double best_t = 0.0;
     for (const Tile& c : cand) {
@@ -899,6 +903,7 @@ BigCfg big_cfg(int M, int N, int K, bool resid, int max_split, bool fused_head) 
             if (S == 5 || S == 7) continue;
             if (S == 1 ? c.ti == 8 && M >= 4096 : t128x192 && M < 4096) continue;
             const long per_cu = (tiles * S + 255) / 256;
+            if (c.ti == 8 && c.tj == 4 && (S > 1 || per_cu > 1)) continue;
             // three 128 x 192 tiles share a CU: they reach their rate when more follow
             const double rate = t128x192 && per_cu <= 3 ? 2.65 : c.rate;
             const double calc = per_cu * ((double)bm * bn * K / S / (1e6 * rate) + c.fixed_us);
@@ -1021,7 +1026,8 @@ hipError_t launch_gemm(int dtype, const void* X, int M, int K, int ldx, const vo
         const dim3 grid(tiles_m * tiles_n, c.split);
 #define DARD_GB(TI, TJ, WM, NST, WD, OCC)                                                                       \
     launch((gemm_big_bf16<TI, TJ, WM, NST, WD, OCC>), grid, dim3(256 * WM), 0, s, x, M, K, w, N, e, tiles_n)
-        if (c.ti == 8) DARD_GB(8, 3, 2, 4, 3, 2);
+        if (c.ti == 8 && c.tj == 4) DARD_GB(8, 2, 2, 4, 4, 2);
+        else if (c.ti == 8) DARD_GB(8, 3, 2, 4, 3, 2);
         else if (c.ti == 6) DARD_GB(12, 2, 1, 3, 3, 2);
         else if (c.ti == 3) DARD_GB(6, 2, 1, 4, 4, 3);
         else if (c.ti == 2) DARD_GB(4, 1, 1, 4, 4, 4);

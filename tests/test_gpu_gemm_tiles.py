@@ -64,6 +64,7 @@ def reference_kv(w, dims, ids):
     (1, 1000, 3584, 18944, (2, 4, 6, 1), (2, 8, 6, 3)),   # 128 x 192; 256 x 192, 3 splits
     (2, 2050, 1024, 4160, (2, 4, 6, 1), (2, 6, 4, 1)),   # 128 x 192; 192 x 128, one split
     (3, 683, 1024, 4160, (2, 4, 6, 1), (2, 6, 4, 2)),   # 192 x 128, 2 splits, added at 2049 rows
+    (3, 513, 4096, 2112, (2, 4, 4, 1), (2, 8, 4, 1)),   # 128 x 128; 256 x 128, one round and one split (O as well)
     (3, 683, 4096, 1088, (2, 6, 4, 1), (2, 8, 6, 1)),   # 192 x 128; 256 x 192, one split (O as well)
 ])
 def test_prefill_tilings(b, P, d, F, gu, down):

@@ -107,14 +107,15 @@ def tile(launch):
 
 # the projections of 4096 and 3584 wide models over row counts on both sides of
 # every change of tile, K too short for a split, and full sums on 256 x 192 tiles
-# (2560 x 4096 x 12288, 8192 x 4096 x 4096, 700 x 320 x 8192)
+# (2560 x 4096 x 12288, 8192 x 4096 x 4096, 700 x 320 x 8192), one round of 256 x 128
+# (1537 to 2048 rows of 4096 columns, 1793 to 2304 of 3584)
 CASES = [(M, d, F) for d, F in ((4096, 12288), (3584, 18944), (1024, 4160))
-         for M in (65, 97, 160, 255, 256, 300, 651, 1000, 2048, 2100, 2560, 2816, 3000, 3500, 4096, 5000, 6000, 8192,
+         for M in (65, 97, 160, 255, 256, 300, 651, 1000, 1536, 1537, 2048, 2049, 2100, 2304, 2305, 2560, 2816, 3000, 3500, 4096, 5000, 6000, 8192,
                    16000)] + [(700, 8192, 320), (700, 512, 128)]
 
 
 def test_tiles_that_run_are_the_tiles_of_the_plan(forwards):
-    full_256 = 0
+    full_256 = one_round = 0
     for (M, d, F), launches in zip(CASES, forwards(CASES)):
         gemms = [x for x in launches if "gemm_big_bf16" in x[0]]
         assert len(gemms) == 4, (M, d, F, launches)   # QKV, O, gate/up, down
@@ -125,7 +126,13 @@ def test_tiles_that_run_are_the_tiles_of_the_plan(forwards):
             assert tile(x) == plan[1:], (M, N, K, x[0], plan)
             assert (x[4] == PARTIAL) == (x[4] in (RESID, PARTIAL) and plan[3] > 1), (M, N, K, x, plan)
             full_256 += x[4] == RESID and tile(x) == (8, 6, 1)
-    assert full_256 >= 3   # the full sums on 256 x 192 tiles are among the cases
+            if tile(x)[:2] == (8, 4):
+                assert x[4] == RESID and x[1] <= 256, (M, d, F, x)
+                one_round += 1
+            # exactly a round of 256 x 128 tiles: two rounds of 128 x 128 took longer
+            assert (M, N, x[4]) != (2048, 4096, RESID) or tile(x) == (8, 4, 1), (K, x)
+    # the full sums on 256 x 192 and 256 x 128 tiles are among the cases
+    assert full_256 >= 3 and one_round >= 6
 
 
 def test_streaming_tiles_that_run_are_the_tiles_of_the_plan(forwards):
