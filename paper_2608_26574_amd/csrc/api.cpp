@@ -131,8 +131,8 @@ WsLayout ws_layout(const dard_dims* d, int b, int B, int cap) {
     W.act = o; o = align256(o + rows * d->ffn_dim * es);
     W.sel = o; o = align256(o + step_rows * ((B + 63) / 64) * 8);   // state mask of the step
     // split-key attention partials: room for the largest split a step picks at
-    // any prefix length the cache holds (0 .. cap - 2B keys); a prefill splits
-    // only as far as this room allows
+    // any prefix length the cache holds (0 .. cap - 2B keys); a prefix pass takes
+    // the split-K partials' buffer instead
     W.part_slots = 0;
     const int max_tiles = attention_tiles(1, cap - 2 * B > 0 ? cap - 2 * B : 0, B, cap);
     for (int t = 1; t <= max_tiles; ++t) {

@@ -859,9 +859,15 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
 // - more than 64 rows per KV head (grouped-query attention, prefill): 4 waves
 //   per group, and a second, phase-shifted key group while the workgroups
 //   alone leave SIMDs idle (7B GQA shape, batch 8: 35.6 -> 31.4 us); while they
-//   cover less than half of the CUs the keys are split, four tiles or more each
-//   (28 heads over 4 KV heads, mask included: one sequence of 1472 + 64 keys 45 ->
-//   23 us, four of 1024 + 64 40 -> 29 us);
+//   cover at most half of the CUs the keys are split, four tiles or more each
+//   (28 heads over 4 KV heads: one sequence of 1472 + 128 keys 40 -> 24 us).  A
+//   split pays about 6 us for its partials and the combine kernel, twice that
+//   with 128 workgroups, and saves about 1 us a tile, so few tiles are left
+//   whole: 512 rows of a prefill, 32 heads, 19 us and 26 split in two; 16
+//   workgroups break even at 11 tiles (22 us both ways), 64 at 13 (26 and 24, and
+//   the wider gap to the next kernel), 84 to 128 between 20 and 24 (32 and 33 at 18
+//   tiles, 41 and 37 at 25).  With the FP8 cache (one key group, so about 5 us a
+//   tile) splits pay from 8 tiles in every case (512 rows: 50 and 39);
 // - 64 rows (one MHA head's augmented block): with at least 256 workgroups,
 //   2 waves per workgroup (batch 16: 36 us); with few heads (batch 1-2), 4
 //   waves and key splits of about 3 tiles merged by the combine kernel
@@ -873,7 +879,7 @@ struct AttnCfg {
     int waves, g, rowtiles, ns, tps;
 };
 
-AttnCfg attention_cfg(int b, int R, int Hq, int Hkv, int ntiles, bool split_ok = true) {
+AttnCfg attention_cfg(int b, int R, int Hq, int Hkv, int ntiles, bool kv_fp8, bool split_ok = true) {
     AttnCfg c{};
     const int nrows = (Hq / Hkv) * R;
     c.g = 1;
@@ -883,7 +889,8 @@ AttnCfg attention_cfg(int b, int R, int Hq, int Hkv, int ntiles, bool split_ok =
         c.rowtiles = (nrows + 127) / 128;
         const long wgs = (long)b * Hkv * c.rowtiles;
         if (wgs * 4 < 1024 && ntiles >= 4) c.g = 2;
-        if (split_ok && wgs * 2 <= 256 && ntiles >= 8) {
+        const int least = kv_fp8 ? 8 : (wgs <= 48 ? 12 : (wgs <= 64 ? 14 : 24));   // tiles worth a split
+        if (split_ok && wgs * 2 <= 256 && ntiles >= least) {
             const long ns = std::min<long>(std::min<long>(256 / wgs, ntiles / 4), kMaxSplit);
             c.ns = (int)ns;
         }
@@ -931,7 +938,7 @@ int attention_tiles(int masked, int P, int B, int nkeys) {
 
 size_t attention_partial_slots(int dtype, int b, int R, int Hq, int Hkv, int ntiles) {
     if (dtype != DARD_DTYPE_BF16 || b < 1 || R < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv) return 0;
-    const AttnCfg c = attention_cfg(b, R, Hq, Hkv, ntiles);
+    const AttnCfg c = attention_cfg(b, R, Hq, Hkv, ntiles, true);   // (the cache format that splits more)
     return c.ns <= 1 ? 0 : (size_t)c.ns * b * R * Hq;
 }
 
@@ -942,11 +949,11 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t s) {
         if (a.masked && (!a.sel || a.B > kMaxBlock)) return hipErrorInvalidValue;
         if (a.dh != 64 && a.dh != 128) return hipErrorInvalidValue;
         const int ntiles = attention_tiles(a.masked, a.P, a.B, a.nkeys);
-        AttnCfg c = attention_cfg(a.b, a.R, a.Hq, a.Hkv, ntiles);
+        AttnCfg c = attention_cfg(a.b, a.R, a.Hq, a.Hkv, ntiles, a.kv_fp8);
         // a split needs room for its partials; without it one workgroup walks every key
         const size_t nrow = (size_t)a.b * a.R * a.Hq;
         if (c.ns > 1 && (!a.part || !a.part_ml || (size_t)c.ns * nrow > a.part_slots))
-            c = attention_cfg(a.b, a.R, a.Hq, a.Hkv, ntiles, false);
+            c = attention_cfg(a.b, a.R, a.Hq, a.Hkv, ntiles, a.kv_fp8, false);
         if (a.kv_fp8 && c.waves == 4) c.g = 1;   // see attention_kernel: one key group with the fp8 cache
         const size_t tiles = (size_t)a.b * a.Hkv * c.rowtiles;
         if (tiles == 0 || tiles > 0x7fffffff) return hipErrorInvalidValue;

@@ -12,7 +12,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("b,B,P,Hq,Hkv,dh", [
     (1, 32, 384, 28, 4, 128),     # 7 tiles: not split
-    (1, 32, 400, 28, 4, 128),     # 8 tiles, ragged prefix end: the shortest split
+    (1, 32, 400, 28, 4, 128),     # 8 tiles, ragged prefix end: not split
+    (1, 32, 650, 28, 4, 128),     # 12 tiles, ragged prefix end: the shortest split
+    (4, 32, 760, 28, 4, 128),     # 64 workgroups, 13 tiles: not split
+    (3, 64, 1390, 28, 4, 128),    # 84 workgroups, 24 tiles: the shortest split there
     (2, 24, 1000, 28, 4, 128),    # ragged block tile in the last split
     (1, 16, 4100, 14, 2, 128),    # 66 tiles: the largest split count
     (4, 64, 700, 8, 2, 64),       # head_dim 64

@@ -146,6 +146,17 @@ def test_streaming_tiles_that_run_are_the_tiles_of_the_plan(forwards):
             assert (nw, x[2]) == (plan[2], plan[3]), (M, d, F, x, plan)
 
 
+def test_few_key_tiles_of_a_prefill_are_not_split(forwards):
+    """Key splits of a prefix pass in bf16: rows (64-key tiles), heads and workgroups on
+    both sides of the rule."""
+    cases = {(449, 4096): 1, (512, 4096): 1, (640, 512): 1, (700, 512): 1, (705, 512): 3, (1024, 1024): 4,
+             (769, 1024): 1, (833, 1024): 3, (1400, 1024): 1, (1473, 1024): 2, (1500, 1536): 1}
+    for ((M, d), ns), launches in zip(cases.items(), forwards([(M, d, 512) for M, d in cases])):
+        att = [x for x in launches if "attn_mfma_kernel" in x[0]]
+        assert len(att) == 1 and att[0][2] == ns, (M, d, att)
+        assert len([x for x in launches if "attn_combine_kernel" in x[0]]) == (ns > 1)
+
+
 def test_partials_are_added_by_a_workgroup_per_row(forwards):
     """From 2048 rows a wave takes a row of the norms that add no partials; those
     that add them keep a workgroup per row at every row count."""
