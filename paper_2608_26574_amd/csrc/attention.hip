@@ -725,7 +725,6 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
     const int si = a.masked ? st[i] : 0;
     const float ci = a.masked ? cf[i] : 0.f;
     float m = -INFINITY, l = 0.f;
-    bool seen = false;                             // a key that the row sees is among this lane's
     for (int k0 = wave * kKeysF; k0 < a.nkeys; k0 += kWavesF * kKeysF) {
         const bool sh = k0 < a.P_sh;               // (P_sh % 64 == 0: whole tiles)
         const float* kk = sh ? kb_sh : kb;
@@ -778,7 +777,6 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
         const float alpha = m == -INFINITY ? 0.f : expf(m - mt);
         // (scores of minus infinity only so far: no weight, whatever other tiles hold)
         const float base = mt == -INFINITY ? 0.f : mt;
-        seen |= vis != 0;
         float ps = 0.f;
 #pragma unroll
         for (int b = 0; b < 2; ++b)
@@ -823,9 +821,7 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
             }
         }
     }
-    // l holds this lane's keys only: sum over the row's four lanes.  Where every
-    // score is minus infinity the softmax is not a number, which l carries
-    if (m == -INFINITY && seen) l = NAN;
+    // l holds this lane's keys only: sum over the row's four lanes
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     __shared__ floatx4 po[kWavesF][NC][64];
@@ -840,11 +836,12 @@ __global__ __launch_bounds__(64 * kWavesF) void attn_f32_kernel(AttnArgs a) {
     float f[kWavesF], lt = 0.f;
 #pragma unroll
     for (int w = 0; w < kWavesF; ++w) {
-        const bool none = pm[w][lr] == -INFINITY;  // (of this wave's keys; of all of them when mm says so)
-        f[w] = none ? 0.f : expf(pm[w][lr] - mm);
-        lt += none ? (mm == -INFINITY ? pl[w][lr] : 0.f) : pl[w][lr] * f[w];
+        f[w] = pm[w][lr] == -INFINITY ? 0.f : expf(pm[w][lr] - mm);
+        lt += pl[w][lr] * f[w];
     }
-    const float inv = lt > 0.f ? 1.f / lt : lt;    // 0 for a row without keys
+    // every row sees a key; where all that it sees score minus infinity, sums and
+    // weights are 0 and 0 / 0 is the softmax
+    const float inv = 1.f / lt;
     if (!row_ok) return;
     float* out = reinterpret_cast<float*>(a.out) + t * DH;
     for (int c = wave; c < NC; c += kWavesF) {
