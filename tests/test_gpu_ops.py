@@ -70,6 +70,24 @@ def test_state_mask_bit_exact(B, flags):
                 assert ((int(got[s, r, j // 64]) >> (j % 64)) & 1) == 0
 
 
+# several rounds of workgroups: four and eight rows a wave, whole and ragged, and
+# blocks too short for them
+@pytest.mark.parametrize("b,B", [(600, 53), (500, 53), (1100, 30), (4100, 32), (9000, 3), (9000, 5), (300, 129)])
+def test_state_mask_many_sequences(b, B):
+    """Every sequence gets the words that it gets alone among few."""
+    announce("mask of many sequences", b, B)
+    rng = np.random.default_rng(B)
+    state = rng.integers(0, 3, size=(8, B)).astype(np.uint8)
+    conf = rng.random((8, B)).astype(np.float32)
+    few = torch.zeros(8, 2 * B, (B + 63) // 64, dtype=torch.int64, device="cuda")
+    dard.dard_build_state_mask(dev(state), dev(conf), 0, few)
+    idx = torch.from_numpy(rng.integers(0, 8, size=b)).cuda()
+    many = torch.full((b, 2 * B, (B + 63) // 64), -1, dtype=torch.int64, device="cuda")
+    dard.dard_build_state_mask(dev(state)[idx].contiguous(), dev(conf)[idx].contiguous(), 0, many)
+    assert torch.equal(many, few[idx])
+
+
+
 # ---------------------------------------------------------------- attention
 def _attn_case(b, B, P, Hq, Hkv, dh, dtype, cand_frac, seed, flags=0, cap_extra=3, sample=None):
     """Max |GPU - oracle| over the sequences in `sample` (all by default)."""
