@@ -189,19 +189,21 @@ __global__ __launch_bounds__(256) void conf_partial_kernel(ConfArgs a, int step_
     }
 }
 
-// kLanes lanes per row: lane `sub` merges chunks sub, sub + kLanes, ..., then a
+// LANES lanes per row: lane `sub` merges chunks sub, sub + LANES, ..., then a
 // butterfly over the row's lanes (the lower lane first on both sides, so all of
-// them hold the same bits).  A row per thread was a chain of one load and one
-// merge per chunk: 360 rows of 19 chunks 5.8 us, 4.6 us now.
+// them hold the same bits).  A row per thread is a chain of one load and one merge
+// per chunk: 360 rows of 19 chunks 5.8 us, 4.6 us with 16 lanes.  With one or two
+// chunks a row per thread it is (4096 rows of one chunk: the whole call 20.3 us, 21.7
+// with 16 lanes).
 constexpr int kLanes = 16, kCombineThreads = 256;
 
-template <bool STATS>
+template <bool STATS, int LANES>
 __global__ __launch_bounds__(kCombineThreads) void conf_combine_kernel(
     const float* __restrict__ part, int rows, int nchunk, int V, const float* __restrict__ ls, int64_t ld,
     const int32_t* __restrict__ cur, int32_t* __restrict__ argmax, float* __restrict__ maxprob,
     float* __restrict__ pcur, float* __restrict__ entropy, float* __restrict__ margin) {
-    const int r = (int)((blockIdx.x * (size_t)kCombineThreads + threadIdx.x) / kLanes);
-    const int sub = threadIdx.x & (kLanes - 1);
+    const int r = (int)((blockIdx.x * (size_t)kCombineThreads + threadIdx.x) / LANES);
+    const int sub = threadIdx.x & (LANES - 1);
     if (r >= rows) return;                         // (whole rows of lanes)
     constexpr int K = STATS ? kConfStatsStride : kConfStride;
     const float* p = part + (size_t)r * nchunk * K;
@@ -211,9 +213,9 @@ __global__ __launch_bounds__(kCombineThreads) void conf_combine_kernel(
         return Acc{q[0], __float_as_int(q[1]), q[2], STATS ? q[3] : 0.f, STATS ? q[4] : -INFINITY};
     };
     Acc t = at(sub);
-    for (int c = sub + kLanes; c < nchunk; c += kLanes) t = merge<STATS>(t, at(c));
+    for (int c = sub + LANES; c < nchunk; c += LANES) t = merge<STATS>(t, at(c));
 #pragma unroll
-    for (int o = 1; o < kLanes; o <<= 1) {
+    for (int o = 1; o < LANES; o <<= 1) {
         Acc y{__shfl_xor(t.m, o, 64), __shfl_xor(t.a, o, 64), __shfl_xor(t.s, o, 64), 0.f, -INFINITY};
         if (STATS) { y.t = __shfl_xor(t.t, o, 64); y.m2 = __shfl_xor(t.m2, o, 64); }
         t = (sub & o) ? merge<STATS>(y, t) : merge<STATS>(t, y);
@@ -286,14 +288,19 @@ hipError_t launch_conf_combine(const float* part, int rows, int nchunk, int V, c
                                const int32_t* cur_tok, int32_t* argmax, float* maxprob, float* pcur,
                                float* entropy, float* margin, hipStream_t s) {
     TraceScope ts(DARD_K_CONFIDENCE, s);
-    constexpr int per_wg = kCombineThreads / kLanes;
-    const dim3 g((rows + per_wg - 1) / per_wg), blk(kCombineThreads);
-    if (entropy || margin)
-        launch(conf_combine_kernel<true>, g, blk, 0, s, part, rows, nchunk, V, ls, ld, cur_tok, argmax, maxprob,
-               pcur, entropy, margin);
-    else
-        launch(conf_combine_kernel<false>, g, blk, 0, s, part, rows, nchunk, V, ls, ld, cur_tok, argmax, maxprob,
-               pcur, entropy, margin);
+    const bool stats = entropy || margin;
+#define DARD_CC(LANES)                                                                                                \
+    do {                                                                                                              \
+        constexpr int per_wg = kCombineThreads / LANES;                                                               \
+        const dim3 g((rows + per_wg - 1) / per_wg), blk(kCombineThreads);                                             \
+        if (stats) launch((conf_combine_kernel<true, LANES>), g, blk, 0, s, part, rows, nchunk, V, ls, ld, cur_tok,   \
+                          argmax, maxprob, pcur, entropy, margin);                                                    \
+        else launch((conf_combine_kernel<false, LANES>), g, blk, 0, s, part, rows, nchunk, V, ls, ld, cur_tok,        \
+                    argmax, maxprob, pcur, entropy, margin);                                                          \
+    } while (0)
+    if (nchunk <= 2) DARD_CC(1);
+    else DARD_CC(kLanes);
+#undef DARD_CC
     return hipGetLastError();
 }
 

@@ -263,7 +263,9 @@ def _conf_ref(ls, lx=None, w=None, cur=None):
     return am, mp, pc
 
 
-@pytest.mark.parametrize("rows,V", [(5, 126464), (3, 152064), (7, 2048), (4, 10), (2, 8195), (1, 1)])
+@pytest.mark.parametrize("rows,V", [(5, 126464), (3, 152064), (7, 2048), (4, 10), (2, 8195), (1, 1),
+                                    # one, two (a row per thread) and three chunks, over several workgroups
+                                    (300, 40), (300, 16384), (300, 16390)])
 def test_confidence_plain(rows, V):
     announce("confidence", rows, V)
     g = torch.Generator().manual_seed(V + rows)
